@@ -811,11 +811,16 @@ int launch_sweeps64_keep(hipStream_t s, const DevGrid& g, int face, const double
     if (use_tb2d(g, count))
         return launch_tb2d<double>(s, g, face, v, rhs, Lam, rC, out, st, count, tau, nullptr, PassSlots{}, stages,
                                    sstride);
+    const int k = b3d_stages(g, count);
+    if (k > 1) {
+        launch_b3d<double>(s, g, face, v, rhs, Lam, rC, out, st, k, tau, nullptr, PassSlots{}, stages, sstride);
+        return k;
+    }
     return -1;
 }
 
 int sweeps_per_launch(const DevGrid& g, int count) {
-    if (!use_tb2d(g, count)) return 1;
+    if (!use_tb2d(g, count)) return b3d_stages(g, count);
     // as few launches as the tile allows, with equal stage counts: a launch
     // of K stages recomputes a ring of width K, so even launches waste least
     const int kmax = g.ny >= TALL_ROWS ? KMAX_TB : KMAX_SHORT;
@@ -832,6 +837,10 @@ int launch_sweeps64(hipStream_t s, const DevGrid& g, int face, const double* v, 
         if (nc_done) *nc_done = with_nc;
         return launch_tb2d<double>(s, g, face, v, rhs, Lam, rC, out, st, count, tau, last ? Tit : nullptr, ps,
                                    nullptr, 0, nullptr, nullptr, nullptr, with_nc ? nc : nullptr);
+    }
+    if (const int k = b3d_stages(g, count); k > 1) {
+        launch_b3d<double>(s, g, face, v, rhs, Lam, rC, out, st, k, tau, last ? Tit : nullptr, ps);
+        return k;
     }
     if (use_z3d(g)) {
         if (last) launch_z3d<double>(s, g, face, v, rhs, Lam, rC, out, StageParam{nullptr, 0.0, 0.0}, tau, Tit, ps);
@@ -864,6 +873,9 @@ int launch_sweeps32(hipStream_t s, const DevGrid& g, int face, const float* w, c
     if (last) {
         if (use_z3d(g)) launch_z3d_final32(s, g, face, w, rhs, Lam32, rC, out64, tau, Tit, ps);
         else launch_final32(s, g, face, w, rhs, Lam32, rC, out64, tau, Tit, ps);
+    } else if (const int k = b3d_stages(g, count); k > 1) {
+        launch_b3d<float>(s, g, face, w, qn, Lam32, rC32, out, st, k, tau, nullptr, PassSlots{});
+        return k;
     } else if (use_z3d(g)) {
         launch_z3d<float>(s, g, face, w, qn, Lam32, rC32, out, one_stage(st), tau, nullptr, PassSlots{});
     } else {
