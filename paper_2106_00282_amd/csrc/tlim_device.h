@@ -221,6 +221,52 @@ static __device__ __forceinline__ void relax_cell(const DevPhases& ph, double ep
     a2 = r.a2;
 }
 
+// relax_cell of an interface cell with T1 = T2 = t and equal p_inf, inline:
+// the same operations as relax_interface, whose quadratic is linear there.
+static __device__ __forceinline__ void relax_equal_pinf(const DevPhases& ph, double t, double m1, double m2,
+                                                        double& T, double& a2) {
+    const double G1 = ph.gamma[0] - 1.0, G2 = ph.gamma[1] - 1.0;
+    const double C1 = m1 * ph.cv[0], C2 = m2 * ph.cv[1];
+    const double t0 = (C1 * t + C2 * t) / (C1 + C2);
+    a2 = (t0 * (G2 * C2)) / (t0 * (G1 * C1 + G2 * C2));
+    T = t0;
+}
+
+// (T/T0)^n of a lane's cells: the exponent is tested once, not per cell.
+template <int RW, int C>
+static __device__ __forceinline__ void pow_rows(const double (&t)[RW][C], double invT0, double n,
+                                                double (&out)[RW][C]) {
+    auto each = [&](auto f) {
+#pragma unroll
+        for (int r = 0; r < RW; ++r)
+#pragma unroll
+            for (int j = 0; j < C; ++j) out[r][j] = f(t[r][j] * invT0);
+    };
+    if (n == 2.0) each([](double x) { return x * x; });
+    else if (n == 0.0) each([](double) { return 1.0; });
+    else if (n == 1.0) each([](double x) { return x; });
+    else if (n == 3.0) each([](double x) { return x * x * x; });
+    else if (n == 2.5) each([](double x) { return x * x * sqrt(x); });
+    else each([n](double x) { return pow_ool(x, n); });
+}
+
+// cell_conductivity_pow of a lane's cells.
+template <int RW, int C>
+static __device__ __forceinline__ void lambda_rows(const DevPhases& ph, const double (&t)[RW][C],
+                                                   const double (&a2)[RW][C], double (&Lam)[RW][C]) {
+    double p[RW][C];
+    pow_rows(t, ph.invT0[0], ph.npow[0], p);
+#pragma unroll
+    for (int r = 0; r < RW; ++r)
+#pragma unroll
+        for (int j = 0; j < C; ++j) Lam[r][j] = (1.0 - a2[r][j]) * (ph.k0[0] * p[r][j]);
+    pow_rows(t, ph.invT0[1], ph.npow[1], p);
+#pragma unroll
+    for (int r = 0; r < RW; ++r)
+#pragma unroll
+        for (int j = 0; j < C; ++j) Lam[r][j] += a2[r][j] * (ph.k0[1] * p[r][j]);
+}
+
 }  // namespace phys
 
 namespace tb {
@@ -264,6 +310,13 @@ static __device__ __forceinline__ int fold(int c, int n, int per) {
         return m < 0 ? m + n : m;
     }
     return c < 0 ? 0 : (c >= n ? n - 1 : c);
+}
+
+// fold for a coordinate that a tile reaches past the grid by less than the
+// grid's size, without a division; smaller grids divide.
+static __device__ __forceinline__ int fold_tile(int c, int n, int per) {
+    if (per && n >= 256) return c < 0 ? c + n : (c >= n ? c - n : c);
+    return fold(c, n, per);
 }
 
 // Folded index of row yg0 + r, given yi0 = fold(yg0): the grids blocked

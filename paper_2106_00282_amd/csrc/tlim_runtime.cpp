@@ -463,7 +463,7 @@ void run_lim_pass(tlim_ctx* c, const DevGrid& g, int face, double tau, const Pas
                 return ps.lam_dev ? tlim::StageParam{ps.lam_dev, 0.0, ps.chat[k]}
                                   : tlim::StageParam{nullptr, ps.tb[k], 0.0};
             };
-            const int k = tlim::sweeps_per_launch(g, nst - 2);
+            const int k = tlim::sweeps_per_launch(g, nst - 2, true);
             if (k > 1)
                 tlim::launch_b3d<float>(s, g, face, nullptr, c->q32, c->Lam32, c->rC32, c->wb[0], ps.at(1), k, tau,
                                         nullptr, tlim::PassSlots{}, nullptr, 0, sp(0));
@@ -475,7 +475,7 @@ void run_lim_pass(tlim_ctx* c, const DevGrid& g, int face, double tau, const Pas
         }
         while (m < upto) {
             // 3D grids: the final stage (in double) has a launch of its own
-            int k = tlim::sweeps_per_launch(g, g3 && m < nst - 1 ? nst - 1 - m : upto - m);
+            int k = tlim::sweeps_per_launch(g, g3 && m < nst - 1 ? nst - 1 - m : upto - m, true);
             bool last = !vh && m + k == nst;
             float* nxt = cur == c->wb[0] ? c->wb[1] : c->wb[0];
             int done = tlim::launch_sweeps32(s, g, face, cur, c->q32, c->Lam32, c->rC32, nxt, ps.at(m), k, last, tau,
@@ -2171,7 +2171,9 @@ tlim_status tlim_adjoint_parabolic(tlim_ctx* c, const tlim_step_opts* o, int32_t
                 std::vector<double> cmv, tbv;
                 int m = nst;
                 while (m >= 1) {
-                    int k = std::min(m, tlim::sweeps_per_launch(g, m));
+                    // (the reverse kernel takes up to 8 stages a launch; equal shares)
+                    const int nl = (m + 7) / 8;
+                    int k = (m + nl - 1) / nl;
                     cmv.assign(k, 0.0);
                     tbv.assign(k, 0.0);
                     for (int q = 0; q < k; ++q) {

@@ -25,8 +25,9 @@ struct Stages {
 };
 
 // Number of stages the next launch will advance when `count` remain (the
-// launches of a pass get equal shares of at most 8 or 10 stages, by tile height).
-int sweeps_per_launch(const DevGrid& g, int count);
+// launches of a pass get equal shares, in as many launches as cost least);
+// f32: stages of the FP32 correction form.
+int sweeps_per_launch(const DevGrid& g, int count, bool f32 = false);
 
 // The next Picard pass's coefficients, built by the launch that reaches the
 // final stage when it can (blocked 2D launches): Lam = sum_k alpha_k

@@ -7,31 +7,28 @@
 // where v is the correction w = v - g).  The final stage (b = 0) of the FP64
 // form is the same update with c = 1.
 //
-// k_tb2d advances K stages per launch.  A workgroup of NW wave64s
-// loads an extended tile once (v, G, Lambda, 1/C; coalesced rows, one per
-// wave and field), builds the four kappa of every cell in registers, and
+// k_tb2d advances K stages per launch.  A workgroup of 16 wave64s loads an
+// extended tile once (v, G, Lambda, 1/C; every row's loads in flight before
+// the first is used), builds the four kappa of every cell in registers, and
 // then runs the K stages out of registers:
-//   - each lane owns C adjacent cells of a row (C = 1 or 2): x-neighbours
-//     come from the lane's own cells or from the adjacent lanes through DPP
-//     wave shifts;
-//   - y-neighbours are the lane's own registers (each lane owns 8/C
-//     consecutive rows), except at the seams between waves, which go
-//     through a double-buffered LDS row (one barrier per stage).
+//   - each lane owns C adjacent cells of a row (C = 1 or 2) in RW consecutive
+//     rows: x-neighbours come from the lane's own cells or from the adjacent
+//     lanes through DPP wave shifts;
+//   - y-neighbours are the lane's own registers, except at the seams between
+//     waves, which go through a double-buffered LDS row (one barrier per
+//     stage).
 // Cells within K of the extended tile's edge go stale one ring per stage;
-// the inner (64C-2K) x (NW*8/C-2K) cells are exact and written out.
-// Grids of at least 128 rows use 16 waves (64 x 128 tiles, or for the float
-// stages on grids of at least 128 columns 128 x 64 tiles with two cells per
-// lane), smaller ones 8 waves (64 x 64, up to 8 stages); one workgroup per
-// CU, up to 10 stages per launch.  Every workgroup of a launch is resident at
-// once on the 1024^2 grids, so a launch costs one load phase plus its stages:
-// the 16-wave tiles halve the halo per stage against 64 x 64 and let a Picard
-// pass of 15-20 stages run in two launches instead of three.  A 64-wide row
-// of floats spans 3 cache lines for 2 lines of data (the rows start where
-// the tile falls), a 128-wide one 5 for 4, and the lane's two cells come in
-// one load: the FP32 form's launches that reach the final stage take 10%
-// less time on the 128 x 64 tiles.  The double kernels gain nothing from
-// them (5 lines for 4 against 9 for 8; the launch that relaxes and builds the
-// next step's start runs slower), so they keep the 64 x 128 tiles.
+// the inner (64C-2K) x (16RW-2K) cells are exact and written out.
+//
+// What bounds it: one workgroup per CU, so a launch is its start (2 us), its
+// load phase, its stages and its epilogue in turn.  The stage loop runs at
+// about the VALU issue rate (per cell and stage in double: 8 operations, and
+// 2 (C = 2) or 4 (C = 1) DPP moves).  On the 1024^2 grid a double launch of 8
+// stages takes 17.5 us on 128 x 64 tiles (20.5 us on 64 x 128 tiles with the
+// rows loaded one round trip after the other, the factor c_m applied per
+// stage and one cell per lane), 25 us with the next pass's coefficients
+// built in its epilogue (33 us), 31 us with the next step's start (39 us).  Smaller grids
+// leave CUs idle on such tiles and take smaller ones (Shape below).
 // Bytes per launch: 4 words read per extended cell + 1 word written per
 // output cell, for K stages.
 #include <hip/hip_runtime.h>
@@ -43,14 +40,61 @@ namespace tlim {
 
 namespace {
 
-using tb::ROWS;
 using tb::row_index;
 using tb::lane_value;
 
-constexpr int KMAX_TB = 10;     // stages per launch, 16-wave tiles
-constexpr int KMAX_SHORT = 8;   // stages per launch, 8-wave tiles
-constexpr int TALL_ROWS = 128;  // grids with at least this many rows use 16-wave tiles
-constexpr int WIDE_COLS = 128;  // ... and 128-wide ones (two cells per lane) with at least this many columns
+constexpr int KMAX_TB = 16;  // stages per launch
+constexpr int NWAVES = 16;   // waves per workgroup
+constexpr int kCUs = 256;
+
+// Tiles of a workgroup: C cells per lane in x by RW rows per wave in y.  A
+// launch of K stages takes about 2 us plus, for each round of one workgroup
+// per CU, base + fill * (share of the CUs with a tile) + K * stage, in us
+// (double, float; fitted to 96^2 .. 2048^2 grids at K = 2 .. 15).  Grids that
+// leave CUs idle on large tiles run on smaller ones: 512 x 300 in double at
+// K = 8 takes 12.7 us on 128 x 64 tiles, 15.5 on 64 x 128, 9.4 on 64 x 64 and
+// 7.2 on 64 x 32; 1024^2 takes 17.8, 19.3, 19.6 and 25.1.
+struct Shape {
+    int c, rw;
+    double base[2], fill[2], stage[2];
+    int ext_x() const { return 64 * c; }
+    int ext_y() const { return NWAVES * rw; }
+};
+enum { S_WIDE, S_TALL, S_SQUARE, S_FLAT, kShapes };
+constexpr Shape kShapeTab[kShapes] = {{2, 4, {5.1, 3.7}, {3.6, 0.9}, {0.76, 0.55}},
+                                      {1, 8, {7.1, 3.9}, {2.6, 0.9}, {0.81, 0.57}},
+                                      {1, 4, {4.0, 2.2}, {1.2, 1.0}, {0.41, 0.38}},
+                                      {1, 2, {2.6, 1.6}, {1.4, 1.4}, {0.32, 0.34}}};
+
+// Cost of a launch of K stages (halo H) on tiles of shape i; 0 where the
+// tile does not apply.
+double launch_cost(const DevGrid& g, int i, int K, int H, bool f32) {
+    const Shape& t = kShapeTab[i];
+    // two cells per lane: a lane's pair must not straddle a periodic wrap
+    if (t.c == 2 && (g.nx < 2 || (g.per[0] && g.nx % 2))) return 0.0;
+    const int hx = t.c == 2 ? (H + 1) & ~1 : H;
+    const int ox = t.ext_x() - 2 * hx, oy = t.ext_y() - 2 * H;
+    if (ox < 4 || oy < 4) return 0.0;
+    const int64_t tiles = (int64_t)((g.nx + ox - 1) / ox) * ((g.ny + oy - 1) / oy);
+    const int64_t rounds = (tiles + kCUs - 1) / kCUs;
+    const double share = tiles < kCUs ? (double)tiles / kCUs : 1.0;
+    return 2.0 + (double)rounds * (t.base[f32] + t.fill[f32] * share + K * t.stage[f32]);
+}
+
+// The shape with the least cost for K stages and halo H.
+int best_shape(const DevGrid& g, int K, int H, bool f32, double* cost = nullptr) {
+    int best = -1;
+    double low = 0.0;
+    for (int i = 0; i < kShapes; ++i) {
+        const double c = launch_cost(g, i, K, H, f32);
+        if (c > 0.0 && (best < 0 || c < low)) {
+            best = i;
+            low = c;
+        }
+    }
+    if (cost) *cost = low;
+    return best;
+}
 using tb::from_left;
 using tb::from_right;
 using tb::fmean;
@@ -97,7 +141,8 @@ struct TBArgs {
     DevPhases ph;
     int nx, ny, perx, pery;
     R wx, wy, tau;
-    int K, H, hx, face, tiles_x, ox, oy;
+    R fx, fy;  // wx, wy, halved for arithmetic face means
+    int K, H, hx, tiles_x, ox, oy;
     int vzero;  // float stages: v is the all-zero start w0 = 0 (not read)
     double taud;
     double tb[KMAX_TB], chat[KMAX_TB];
@@ -108,15 +153,18 @@ struct TBArgs {
 // power-law kernels).  C: cells per lane along x (1: 64-wide tiles of 8 rows
 // per wave; 2: 128-wide tiles of 4 rows per wave, lane l owning cells 2l and
 // 2l + 1, so that one of each cell's x-neighbours is in the lane itself).
-template <typename R, int NW, int C, bool kKeep, bool kSH>
+template <typename R, int NW, int RW, int C, bool kKeep, bool kSH, bool kHarm>
 __global__ void __launch_bounds__(64 * NW, 4) k_tb2d(TBArgs<R> a) {
     constexpr int WAVES = NW;
-    constexpr int RW = ROWS / C;       // rows per wave
     constexpr int EXT_X = 64 * C;
     constexpr int EXT_Y = NW * RW;
     __shared__ R sh_lo[2][WAVES][C][64];  // row 0 of each wave (the "up" row of the wave below)
     __shared__ R sh_hi[2][WAVES][C][64];  // row RW-1 of each wave (the "down" row of the wave above)
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    constexpr int face = kHarm ? 1 : 0;
+    const int lane = threadIdx.x & 63;
+    // the wave's number in a scalar register: rows, their addresses and their
+    // wall tests are then scalar work
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     // Lambda of a cell in the epilogues (rho = m1 + m2 used only under the
     // Spitzer-Harm law)
     auto law = [&](double t, double a2, double m1, double m2) -> double {
@@ -137,7 +185,6 @@ __global__ void __launch_bounds__(64 * NW, 4) k_tb2d(TBArgs<R> a) {
     const int tile = tb::xcd_block();
     const int tx = tile % a.tiles_x, ty = tile / a.tiles_x;
     const int yg0 = ty * a.oy - H + wv * RW;
-    const int yi0 = fold(yg0, a.ny, a.pery);
     int xg[C], xi[C];
     bool fL[C], fR[C];
     // output column: cell j of this lane is at least HX in from the tile's x edges
@@ -146,7 +193,7 @@ __global__ void __launch_bounds__(64 * NW, 4) k_tb2d(TBArgs<R> a) {
     for (int j = 0; j < C; ++j) {
         const int xl = C * lane + j;
         xg[j] = tx * a.ox - HX + xl;
-        xi[j] = fold(xg[j], a.nx, a.perx);
+        xi[j] = tb::fold_tile(xg[j], a.nx, a.perx);
         const bool inx = xg[j] >= 0 && xg[j] < a.nx;
         fL[j] = a.perx ? a.nx > 1 : (inx && xg[j] > 0);
         fR[j] = a.perx ? a.nx > 1 : (inx && xg[j] < a.nx - 1);
@@ -155,24 +202,44 @@ __global__ void __launch_bounds__(64 * NW, 4) k_tb2d(TBArgs<R> a) {
     // Two cells per lane come in one load of two words at column sx: the
     // pair (xi0, xi0 + 1) away from the walls, the clamped copies (both the
     // wall cell) beyond them; sel_j tells which word is cell j.
-    const int sx = C == 2 ? min(xi[0], a.nx - 2) : xi[0];
+    const unsigned sx = (unsigned)(C == 2 ? min(xi[0], a.nx - 2) : xi[0]);
     bool sel[C];
 #pragma unroll
-    for (int j = 0; j < C; ++j) sel[j] = xi[j] == sx;
-    // first word of row r of the tile's lane (formed once per row: every
-    // field's load of the row shares it)
-    auto row_at = [&](int r) -> int64_t { return (int64_t)row_index(yi0, yg0, r, a.ny, a.pery) * a.nx + sx; };
-    auto ld = [&](const auto* f, int64_t o, auto (&out)[C]) {
+    for (int j = 0; j < C; ++j) sel[j] = xi[j] == (int)sx;
+    // first word of each row in a field (scalar: every field's load of the
+    // row takes it as its base, with the lane's column as the offset)
+    int yr[RW];
+    const int yi0 = fold(yg0, a.ny, a.pery);
+#pragma unroll
+    for (int r = 0; r < RW; ++r) yr[r] = row_index(yi0, yg0, r, a.ny, a.pery);
+    auto row = [&](auto* f, int r) { return f + (int64_t)yr[r] * a.nx; };
+    auto ld = [&](const auto* f, int r, auto (&out)[C]) {
         if constexpr (C == 1) {
-            out[0] = f[o];
+            out[0] = row(f, r)[sx];
         } else {
             using T = std::remove_cv_t<std::remove_reference_t<decltype(f[0])>>;
             struct alignas(sizeof(T)) Pair { T x, y; } pr;
-            __builtin_memcpy(&pr, f + o, sizeof(Pair));
+            __builtin_memcpy(&pr, row(f, r) + sx, sizeof(Pair));
 #pragma unroll
             for (int j = 0; j < C; ++j) out[j] = sel[j] ? pr.x : pr.y;
         }
     };
+    // this lane's output cells of row r (C = 2: both in one store; the second
+    // is past the grid only at the right end of an odd width)
+    auto put = [&](auto* f, int r, const auto (&x)[C]) {
+        if constexpr (C == 1) {
+            if (xo[0]) row(f, r)[(unsigned)xg[0]] = x[0];
+        } else {
+            using T = std::remove_reference_t<decltype(f[0])>;
+            struct alignas(sizeof(T)) Pair { T x, y; } pr{x[0], x[1]};
+            if (xo[1]) __builtin_memcpy(row(f, r) + (unsigned)xg[0], &pr, sizeof(Pair));
+            else if (xo[0]) row(f, r)[(unsigned)xg[0]] = x[0];
+        }
+    };
+    // wave-uniform: the face between rows y and y + 1 exists (the grids blocked
+    // here have more than one row)
+    const int ylo = a.pery ? -(1 << 30) : 0, yhi = a.pery ? 1 << 30 : a.ny - 1;
+    auto face_above = [&](int y) { return (int)(y >= ylo) & (int)(y < yhi); };
     auto yout = [&](int r) { const int row = wv * RW + r; return row >= H && row < EXT_Y - H && yg0 + r < a.ny; };
 
     constexpr bool kFloat = sizeof(R) == 4;
@@ -181,103 +248,89 @@ __global__ void __launch_bounds__(64 * NW, 4) k_tb2d(TBArgs<R> a) {
     // gives c_0 G exactly: v is then not read, and that stage is c_0 G.
     const bool vz = kFloat && !kKeep && a.vzero && a.v != a.G && (fin ? K - 1 : K) >= 1;
     // In double the source G lives in LDS (read once per cell and stage):
-    // the four kappa and v already take 80 of the 128 VGPRs that four
-    // workgroups per CU leave, and G in registers spills.
-    constexpr bool kGinLds = !kFloat;
+    // with 8 rows per wave the four kappa and v already take 80 of the 128
+    // VGPRs that four waves per SIMD leave, and G in registers spills.
+    constexpr bool kGinLds = !kFloat && RW * C == 8;
     __shared__ R sG[kGinLds ? EXT_Y : 1][C][64];
     R v[RW][C], G[RW][C], kL[RW][C], kR[RW][C], kD[RW][C], kU[RW][C];
     const bool same = a.v == a.G;
     R Lk[RW][C];     // cell conductivities, kept for a fused FP64 final stage
     R Ldk[C], Luk[C];
+    double lamr[kSlots / 64] = {};  // lambda_G of the pass: its accumulator row (every wave folds it)
     {
+        // Every row's words are in flight before the first is used.  Waiting
+        // row by row (as the compiler does when the first use of a row's word
+        // comes before the next row's loads) costs one memory round trip per
+        // row: the load phase of a 64 x 128 tile took 11 us that way.
         R L[RW][C], t[RW][C];
-        if constexpr (kFloat) {
-            // every row's words in flight before the first is used (the
-            // double kernels load row by row, as in the epilogue)
+        if (a.lam) {
 #pragma unroll
-            for (int r = 0; r < RW; ++r) {
-                const int64_t o = row_at(r);
-                if (vz) {
-#pragma unroll
-                    for (int j = 0; j < C; ++j) v[r][j] = R(0);
-                } else {
-                    ld(a.v, o, v[r]);
-                }
-                ld(a.Lam, o, L[r]);
-                ld(a.rC, o, t[r]);
-            }
-            // the first launch of a pass starts from v^(0) = T^n = g
-            if (same) {
-#pragma unroll
-                for (int r = 0; r < RW; ++r)
-#pragma unroll
-                    for (int j = 0; j < C; ++j) G[r][j] = v[r][j];
-            } else {
-#pragma unroll
-                for (int r = 0; r < RW; ++r) ld(a.G, row_at(r), G[r]);
-            }
-#pragma unroll
-            for (int r = 0; r < RW; ++r)
-#pragma unroll
-                for (int j = 0; j < C; ++j) t[r][j] = a.tau * t[r][j];
-        } else {
-#pragma unroll
-            for (int r = 0; r < RW; ++r) {
-                const int64_t o = row_at(r);
-                // the first launch of a pass starts from v^(0) = T^n = g (G
-                // is then not read)
-                if constexpr (C == 1) {
-                    v[r][0] = a.v[o];
-                    sG[wv * RW + r][0][lane] = same ? v[r][0] : a.G[o];
-                    L[r][0] = a.Lam[o];
-                    t[r][0] = a.tau * a.rC[o];
-                    continue;
-                }
-                R Gr[C];
-                ld(a.v, o, v[r]);
-                if (same) {
-#pragma unroll
-                    for (int j = 0; j < C; ++j) Gr[j] = v[r][j];
-                } else {
-                    ld(a.G, o, Gr);
-                }
-                ld(a.Lam, o, L[r]);
-                ld(a.rC, o, t[r]);
-#pragma unroll
-                for (int j = 0; j < C; ++j) {
-                    sG[wv * RW + r][j][lane] = Gr[j];
-                    t[r][j] = a.tau * t[r][j];
-                }
-            }
+            for (int k = 0; k < kSlots / 64; ++k) lamr[k] = a.lam[lane + 64 * k];
         }
+#pragma unroll
+        for (int r = 0; r < RW; ++r) {
+            ld(a.Lam, r, L[r]);
+            ld(a.rC, r, t[r]);
+            ld(a.G, r, G[r]);
+        }
+        // the first launch of a pass starts from v^(0) = T^n = g
+        if (!same && !vz) {
+#pragma unroll
+            for (int r = 0; r < RW; ++r) ld(a.v, r, v[r]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int j = 0; j < C; ++j) {
             sh_lo[0][wv][j][lane] = L[0][j];
             sh_hi[0][wv][j][lane] = L[RW - 1][j];
         }
+        if constexpr (kGinLds) {
+#pragma unroll
+            for (int r = 0; r < RW; ++r)
+#pragma unroll
+                for (int j = 0; j < C; ++j) sG[wv * RW + r][j][lane] = G[r][j];
+        }
         __syncthreads();
         R Ldn[C], Lup[C];
 #pragma unroll
         for (int j = 0; j < C; ++j) {
-            Ldn[j] = wv > 0 ? sh_hi[0][wv - 1][j][lane] : L[0][j];
-            Lup[j] = wv < WAVES - 1 ? sh_lo[0][wv + 1][j][lane] : L[RW - 1][j];
+            Ldn[j] = wv > 0 ? sh_hi[0][wv > 0 ? wv - 1 : 0][j][lane] : L[0][j];
+            Lup[j] = wv < WAVES - 1 ? sh_lo[0][wv < WAVES - 1 ? wv + 1 : wv][j][lane] : L[RW - 1][j];
         }
+        // arithmetic means: the sum of a face's two cells is formed once (its
+        // half goes into the weight, which is exact)
+        auto mean = [&](R x, R y) { return kHarm ? fmean<R>(x, y, 1) : x + y; };
+        R Mdn[C];
+#pragma unroll
+        for (int j = 0; j < C; ++j) Mdn[j] = mean(L[0][j], Ldn[j]);
 #pragma unroll
         for (int r = 0; r < RW; ++r) {
-            const int y = yg0 + r;
-            const bool iny = y >= 0 && y < a.ny;
-            const bool fD = a.pery ? a.ny > 1 : (iny && y > 0);
-            const bool fU = a.pery ? a.ny > 1 : (iny && y < a.ny - 1);
+            const R wD = face_above(yg0 + r - 1) ? a.fy : R(0), wU = face_above(yg0 + r) ? a.fy : R(0);
+            R Mrt[C];
+#pragma unroll
+            for (int j = 0; j < C; ++j) Mrt[j] = mean(L[r][j], right_of(L[r], j));
 #pragma unroll
             for (int j = 0; j < C; ++j) {
-                const R Ll = left_of(L[r], j), Lr = right_of(L[r], j);
-                const R Ld = r > 0 ? L[r - 1][j] : Ldn[j];
-                const R Lu = r < RW - 1 ? L[r + 1][j] : Lup[j];
-                kL[r][j] = fL[j] ? t[r][j] * a.wx * fmean<R>(L[r][j], Ll, a.face) : R(0);
-                kR[r][j] = fR[j] ? t[r][j] * a.wx * fmean<R>(L[r][j], Lr, a.face) : R(0);
-                kD[r][j] = fD ? t[r][j] * a.wy * fmean<R>(L[r][j], Ld, a.face) : R(0);
-                kU[r][j] = fU ? t[r][j] * a.wy * fmean<R>(L[r][j], Lu, a.face) : R(0);
+                const R tr = a.tau * t[r][j];
+                const R Mup = mean(L[r][j], r < RW - 1 ? L[r < RW - 1 ? r + 1 : r][j] : Lup[j]);
+                const R Mlf = left_of(Mrt, j);  // (every lane takes part)
+                kL[r][j] = tr * (fL[j] ? a.fx : R(0)) * Mlf;
+                kR[r][j] = tr * (fR[j] ? a.fx : R(0)) * Mrt[j];
+                kD[r][j] = tr * wD * Mdn[j];
+                kU[r][j] = tr * wU * Mup;
+                Mdn[j] = Mup;
             }
+            // (row by row: interleaved over all rows, this spills)
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if (same || vz) {
+#pragma unroll
+            for (int r = 0; r < RW; ++r)
+#pragma unroll
+                for (int j = 0; j < C; ++j) {
+                    if constexpr (kGinLds) v[r][j] = sG[wv * RW + r][j][lane];
+                    else v[r][j] = vz ? R(0) : G[r][j];
+                }
         }
         if constexpr (kFloat) {
 #pragma unroll
@@ -291,11 +344,10 @@ __global__ void __launch_bounds__(64 * NW, 4) k_tb2d(TBArgs<R> a) {
             }
         }
     }
-    // lambda_G of the pass from its accumulator row (every wave folds it)
     double lamv = 0.0;
     if (a.lam) {
 #pragma unroll
-        for (int k = 0; k < kSlots / 64; ++k) lamv = fmax(lamv, a.lam[lane + 64 * k]);
+        for (int k = 0; k < kSlots / 64; ++k) lamv = fmax(lamv, lamr[k]);
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) lamv = fmax(lamv, __shfl_xor(lamv, o, 64));
     }
@@ -306,9 +358,25 @@ __global__ void __launch_bounds__(64 * NW, 4) k_tb2d(TBArgs<R> a) {
         ptb = a.lam ? a.taud * lamv * a.chat[lane] : a.tb[lane];
         pcm = 1.0 / (1.0 + ptb);
     }
+    // In double the stages run on V^(s) = Q_s v^(s), Q_s = prod_{k<s} (1 + tau b_k):
+    //   V^(s+1) = Q_s G + tau b_s V^(s) - sum_f kappa_f (V_a - V_f)^(s),
+    // one product per cell and stage less than with the factor c_s.  Lane s
+    // holds Q_s and 1/Q_(s+1) (10 factors of at most 1 + tau lambda).
+    double pQ = 1.0, piQ = 1.0;
+    if constexpr (!kFloat) {
+        double inc = 1.0 + ptb;  // inclusive product over the lanes up to this one
+#pragma unroll
+        for (int o = 1; o < 16; o <<= 1) {
+            const double up = __shfl_up(inc, o, 64);
+            if (lane >= o) inc *= up;
+        }
+        const double below = __shfl_up(inc, 1, 64);
+        pQ = lane == 0 ? 1.0 : below;
+        piQ = 1.0 / inc;
+    }
     // Stage s exchanges the seam rows through LDS buffer (s+1)&1; buffer 0
     // held the Lambda seams, whose reads all precede the first barrier below.
-    // The end waves read a valid row and discard it (no branch).
+    // The end waves read a row of their own: their outer rows go stale anyway.
     const int Kin = fin ? K - 1 : K;
     const int wdn = wv > 0 ? wv - 1 : 0, wup = wv < WAVES - 1 ? wv + 1 : wv;
     // from w0 = 0 the first stage is c_0 G (the same number the stage below
@@ -331,49 +399,67 @@ __global__ void __launch_bounds__(64 * NW, 4) k_tb2d(TBArgs<R> a) {
             sh_hi[buf][wv][j][lane] = v[RW - 1][j];
         }
         __syncthreads();
-        R vup[C], ddn[C];
+        R vup[C], vdn[C];
 #pragma unroll
         for (int j = 0; j < C; ++j) {
-            const R sdn = sh_hi[buf][wdn][j][lane], sup = sh_lo[buf][wup][j][lane];
-            const R vdn = wv > 0 ? sdn : v[0][j];
-            vup[j] = wv < WAVES - 1 ? sup : v[RW - 1][j];
-            ddn[j] = v[0][j] - vdn;
+            vdn[j] = sh_hi[buf][wdn][j][lane];
+            vup[j] = sh_lo[buf][wup][j][lane];
         }
         const double tbd = lane_value(ptb, s);
-        const R cm = (R)lane_value(pcm, s), tb = (R)tbd;
+        const R cm = (R)lane_value(kFloat ? pcm : pQ, s), tb = (R)tbd;
         // Each face difference is formed once and shared by the face's two
         // cells: c - c_left is minus the left neighbour's c - c_right, and
         // c - c_below minus the row below's c - c_above (exact in floating
         // point, so S is the same number as with four differences per cell).
+        // The rows run from the second one up and the first one comes last,
+        // so the seam rows are on their way from LDS meanwhile.
+        R d0[C], ddn[C];
 #pragma unroll
-        for (int r = 0; r < RW; ++r) {
+        for (int j = 0; j < C; ++j) {
+            d0[j] = v[0][j] - v[1][j];
+            ddn[j] = -d0[j];
+        }
+#pragma unroll
+        for (int q = 1; q <= RW; ++q) {
+            const int r = q == RW ? 0 : q;
             R drt[C];
 #pragma unroll
             for (int j = 0; j < C; ++j) drt[j] = v[r][j] - right_of(v[r], j);
 #pragma unroll
             for (int j = 0; j < C; ++j) {
                 const R c = v[r][j];
-                const R up = r < RW - 1 ? v[r + 1][j] : vup[j];
                 const R dlf = -left_of(drt, j);
-                const R dup = c - up;
-                const R S = kL[r][j] * dlf + kR[r][j] * drt[j] + kD[r][j] * ddn[j] + kU[r][j] * dup;
+                const R dup = r == 0 ? d0[j] : c - (r < RW - 1 ? v[r < RW - 1 ? r + 1 : r][j] : vup[j]);
+                const R dd = r == 0 ? c - vdn[j] : ddn[j];
+                const R S = kL[r][j] * dlf + kR[r][j] * drt[j] + kD[r][j] * dd + kU[r][j] * dup;
                 R Gr;
                 if constexpr (kGinLds) Gr = sG[wv * RW + r][j][lane];
                 else Gr = G[r][j];
-                v[r][j] = cm * (Gr + tb * c - S);
+                if constexpr (kFloat) v[r][j] = cm * (Gr + tb * c - S);
+                else v[r][j] = cm * Gr + (tb * c - S);
                 ddn[j] = -dup;
             }
         }
         // the output cells are exact after every stage: keep the intermediate
         // stages when asked (the adjoint's recomputation)
         if (kKeep && s + 1 < K) {
+            const R iq = (R)lane_value(piQ, s);
             R* dst = a.stages + (int64_t)(s + 1) * a.sstride;
 #pragma unroll
-            for (int r = 0; r < RW; ++r)
+            for (int r = 0; r < RW; ++r) {
+                R x[C];
 #pragma unroll
-                for (int j = 0; j < C; ++j)
-                    if (xo[j] && yout(r)) dst[(int64_t)(yg0 + r) * a.nx + xg[j]] = v[r][j];
+                for (int j = 0; j < C; ++j) x[j] = v[r][j] * iq;
+                if (yout(r)) put(dst, r, x);
+            }
         }
+    }
+    if constexpr (!kFloat) {
+        const double iq = lane_value(piQ, K - 1);
+#pragma unroll
+        for (int r = 0; r < RW; ++r)
+#pragma unroll
+            for (int j = 0; j < C; ++j) v[r][j] *= iq;
     }
     // Final stage (b = 0) of the FP32 correction form, in double on v = g + w:
     // T = g - tau rC64 sum_f w_f mean(Lambda'_a, Lambda'_b) (v_a - v_b), with
@@ -385,7 +471,7 @@ __global__ void __launch_bounds__(64 * NW, 4) k_tb2d(TBArgs<R> a) {
             __shared__ double dsh_lo[WAVES][C][64], dsh_hi[WAVES][C][64];
             double vf[RW][C];
 #pragma unroll
-            for (int r = 0; r < RW; ++r) ld(a.g64, row_at(r), gfin[r]);
+            for (int r = 0; r < RW; ++r) ld(a.g64, r, gfin[r]);
 #pragma unroll
             for (int r = 0; r < RW; ++r)
 #pragma unroll
@@ -419,16 +505,16 @@ __global__ void __launch_bounds__(64 * NW, 4) k_tb2d(TBArgs<R> a) {
                     const double Lu = (double)(r < RW - 1 ? Lk[r + 1][j] : Luk[j]);
                     const double lf = left_of(vf[r], j), rt = right_of(vf[r], j);
                     double S = 0.0;
-                    if (fL[j]) S += wxd * fmean<double>(La, Ll, a.face) * (c - lf);
-                    if (fR[j]) S += wxd * fmean<double>(La, Lr, a.face) * (c - rt);
-                    if (fD) S += wyd * fmean<double>(La, Ld, a.face) * (c - prev[j]);
-                    if (fU) S += wyd * fmean<double>(La, Lu, a.face) * (c - up);
+                    if (fL[j]) S += wxd * fmean<double>(La, Ll, face) * (c - lf);
+                    if (fR[j]) S += wxd * fmean<double>(La, Lr, face) * (c - rt);
+                    if (fD) S += wyd * fmean<double>(La, Ld, face) * (c - prev[j]);
+                    if (fU) S += wyd * fmean<double>(La, Lu, face) * (c - up);
                     prev[j] = c;
                     Tfin[r][j] = S;
                 }
             }
 #pragma unroll
-            for (int r = 0; r < RW; ++r) ld(a.rC64, row_at(r), rcfin[r]);
+            for (int r = 0; r < RW; ++r) ld(a.rC64, r, rcfin[r]);
 #pragma unroll
             for (int r = 0; r < RW; ++r)
 #pragma unroll
@@ -442,11 +528,10 @@ __global__ void __launch_bounds__(64 * NW, 4) k_tb2d(TBArgs<R> a) {
                 double Ln[RW][C], a2v[RW][C], m1v[RW][C], m2v[RW][C];
 #pragma unroll
                 for (int r = 0; r < RW; ++r) {
-                    const int64_t o = row_at(r);
-                    ld(a.alpha2, o, a2v[r]);
+                    ld(a.alpha2, r, a2v[r]);
                     if constexpr (kSH) {
-                        ld(a.m1, o, m1v[r]);
-                        ld(a.m2, o, m2v[r]);
+                        ld(a.m1, r, m1v[r]);
+                        ld(a.m2, r, m2v[r]);
                     } else {
 #pragma unroll
                         for (int j = 0; j < C; ++j) m1v[r][j] = m2v[r][j] = 0.0;
@@ -496,17 +581,17 @@ __global__ void __launch_bounds__(64 * NW, 4) k_tb2d(TBArgs<R> a) {
                             const bool fU = a.pery ? a.ny > 1 : y < a.ny - 1;
                             const int64_t o = (int64_t)y * a.nx + xg[j];
                             double d = 0.0;
-                            if (fL[j]) d += wxd * fmean<double>(L, Ll, a.face);
-                            if (fR[j]) d += wxd * fmean<double>(L, Lr, a.face);
-                            if (fD) d += wyd * fmean<double>(L, Ld, a.face);
-                            if (fU) d += wyd * fmean<double>(L, Lu, a.face);
+                            if (fL[j]) d += wxd * fmean<double>(L, Ll, face);
+                            if (fR[j]) d += wxd * fmean<double>(L, Lr, face);
+                            if (fD) d += wyd * fmean<double>(L, Ld, face);
+                            if (fU) d += wyd * fmean<double>(L, Lu, face);
                             bound = fmax(bound, 2.0 * d * rcfin[r][j]);
                             const double La = (double)Lf[j], rf = (double)(float)rcfin[r][j], ga = gfin[r][j];
                             double Sq = 0.0;
-                            if (fL[j]) Sq += wxd * fmean<double>(La, (double)Llf, a.face) * (ga - gl);
-                            if (fR[j]) Sq += wxd * fmean<double>(La, (double)Lrf, a.face) * (ga - gr);
-                            if (fD) Sq += wyd * fmean<double>(La, (double)(float)Ld, a.face) * (ga - gd);
-                            if (fU) Sq += wyd * fmean<double>(La, (double)(float)Lu, a.face) * (ga - gu);
+                            if (fL[j]) Sq += wxd * fmean<double>(La, (double)Llf, face) * (ga - gl);
+                            if (fR[j]) Sq += wxd * fmean<double>(La, (double)Lrf, face) * (ga - gr);
+                            if (fD) Sq += wyd * fmean<double>(La, (double)(float)Ld, face) * (ga - gd);
+                            if (fU) Sq += wyd * fmean<double>(La, (double)(float)Lu, face) * (ga - gu);
                             a.Lam32_next[o] = Lf[j];
                             a.q32_next[o] = (float)(-a.taud * rf * Sq);
                         }
@@ -525,66 +610,60 @@ __global__ void __launch_bounds__(64 * NW, 4) k_tb2d(TBArgs<R> a) {
     double dmax = 0.0, tmax = 0.0, bad = 0.0;
     // the first pass's previous iterate is T^n = g, already on chip
     const bool tit_is_g = kFloat ? (fin && a.Tit == a.g64) : (const void*)a.Tit == (const void*)a.G;
-    // Float kernels read the epilogue's words of every row up front, before
-    // any is used (bit r*C + j of outm: cell j of row r of this lane is an
-    // output cell).  The double kernels read them row by row: there the
-    // registers that batching takes cost more than the load order gains
-    // (measured).
-    unsigned outm = 0;
+    // Words of the epilogue are read for every row before the first is used.
+    // Output cells: rows yo (scalar), columns xo; lanes beyond them read the
+    // row's first word and discard it.
+    bool yo[RW];
 #pragma unroll
-    for (int r = 0; r < RW; ++r)
+    for (int r = 0; r < RW; ++r) yo[r] = yout(r);
+    unsigned xs[C];
 #pragma unroll
-        for (int j = 0; j < C; ++j)
-            if (xo[j] && yout(r)) outm |= 1u << (r * C + j);
-    auto out_at = [&](int r, int j) -> int64_t {
-        return (outm >> (r * C + j)) & 1u ? (int64_t)(yg0 + r) * a.nx + xg[j] : 0;
-    };
-    double titv[RW][C];
+    for (int j = 0; j < C; ++j) xs[j] = xo[j] ? (unsigned)xg[j] : 0u;
+    if (a.Tit) {
+        if (a.ps.dmax) {  // the Picard change only where asked for
+            double titv[RW][C];
+            if (!tit_is_g) {
 #pragma unroll
-    for (int r = 0; r < RW; ++r)
+                for (int r = 0; r < RW; ++r)
 #pragma unroll
-        for (int j = 0; j < C; ++j) titv[r][j] = 0.0;
-    if constexpr (kFloat) {
-        if (a.Tit && a.ps.dmax && !tit_is_g) {
+                    for (int j = 0; j < C; ++j) titv[r][j] = row(a.Tit, r)[xs[j]];
+            } else {
+#pragma unroll
+                for (int r = 0; r < RW; ++r)
+#pragma unroll
+                    for (int j = 0; j < C; ++j) {
+                        if constexpr (kFloat) titv[r][j] = gfin[r][j];
+                        else if constexpr (kGinLds) titv[r][j] = (double)sG[wv * RW + r][j][lane];
+                        else titv[r][j] = (double)G[r][j];
+                    }
+            }
 #pragma unroll
             for (int r = 0; r < RW; ++r)
 #pragma unroll
-                for (int j = 0; j < C; ++j) titv[r][j] = a.Tit[out_at(r, j)];
+                for (int j = 0; j < C; ++j) {
+                    const double tn = fin ? Tfin[r][j] : (double)v[r][j];
+                    dmax = fmax(dmax, yo[r] && xo[j] ? fabs(tn - titv[r][j]) : 0.0);
+                }
         }
-    }
 #pragma unroll
-    for (int r = 0; r < RW; ++r)
+        for (int r = 0; r < RW; ++r)
 #pragma unroll
-        for (int j = 0; j < C; ++j) {
-            if ((outm >> (r * C + j)) & 1u) {
-                const int64_t o = (int64_t)(yg0 + r) * a.nx + xg[j];
-                double tnew;
-                if (fin) {
-                    tnew = Tfin[r][j];
-                    a.out64[o] = tnew;
-                } else {
-                    a.out[o] = v[r][j];
-                    tnew = (double)v[r][j];
-                }
-                if (a.Tit) {
-                    const double tn = tnew;
-                    // the Picard change only where asked for (ps.dmax set)
-                    if (a.ps.dmax) {
-                        double tit;
-                        if (tit_is_g) {
-                            if constexpr (kFloat) tit = gfin[r][j];
-                            else tit = (double)sG[wv * RW + r][j][lane];
-                        } else {
-                            if constexpr (kFloat) tit = titv[r][j];
-                            else tit = a.Tit[o];
-                        }
-                        dmax = fmax(dmax, fabs(tn - tit));
-                    }
-                    tmax = fmax(tmax, fabs(tn));
-                    if (!(tn > 0.0) || isinf(tn)) bad += 1.0;
-                }
+            for (int j = 0; j < C; ++j) {
+                const double tn = fin ? Tfin[r][j] : (double)v[r][j];
+                const bool o = yo[r] && xo[j];
+                tmax = fmax(tmax, o ? fabs(tn) : 0.0);
+                bad += o && (!(tn > 0.0) || isinf(tn)) ? 1.0 : 0.0;
             }
-        }
+    }
+    if (fin) {
+#pragma unroll
+        for (int r = 0; r < RW; ++r)
+            if (yo[r]) put(a.out64, r, Tfin[r]);
+    } else {
+#pragma unroll
+        for (int r = 0; r < RW; ++r)
+            if (yo[r]) put(a.out, r, v[r]);
+    }
     if (a.Tit) {
         // wave-level fold, then lane 0 of every wave adds to a slot of the rows
 #pragma unroll
@@ -613,38 +692,43 @@ __global__ void __launch_bounds__(64 * NW, 4) k_tb2d(TBArgs<R> a) {
             // The partial densities enter only the relaxation of interface
             // cells (pure cells keep their T and alpha2) and the Spitzer-Harm
             // law; 1/C, which they also fix, is the step's own (equal p_inf),
-            // so under the power law they are read in interface cells only.
-            double Ln[RW][C], Tr[RW][C], ar[RW][C];
+            // so under the power law they are read in interface cells only
+            // (the other lanes read the row's first word).
+            double Ln[RW][C], a2v[RW][C], m1v[RW][C], m2v[RW][C];
 #pragma unroll
-            for (int r = 0; r < RW; ++r) {
-                double a2v[C], m1[C], m2[C];
-                const int64_t o = row_at(r);
-                ld(a.alpha2, o, a2v);
-                if constexpr (kSH) {
-                    ld(a.m1, o, m1);
-                    ld(a.m2, o, m2);
-                } else if (next_step) {
+            for (int r = 0; r < RW; ++r) ld(a.alpha2, r, a2v[r]);
+            if constexpr (kSH) {
+#pragma unroll
+                for (int r = 0; r < RW; ++r) {
+                    ld(a.m1, r, m1v[r]);
+                    ld(a.m2, r, m2v[r]);
+                }
+            } else if (next_step) {
+#pragma unroll
+                for (int r = 0; r < RW; ++r)
 #pragma unroll
                     for (int j = 0; j < C; ++j) {
-                        m1[j] = m2[j] = 0.0;
-                        if (phys::is_mixed(a2v[j], a.eps)) {
-                            const int64_t oj = o + (sel[j] ? 0 : 1);
-                            m1[j] = a.m1[oj];
-                            m2[j] = a.m2[oj];
-                        }
+                        const bool mx = phys::is_mixed(a2v[r][j], a.eps);
+                        const unsigned xm = mx ? sx + (sel[j] ? 0u : 1u) : 0u;
+                        m1v[r][j] = row(a.m1, r)[xm];
+                        m2v[r][j] = row(a.m2, r)[xm];
                     }
-                }
+            }
+            if (next_step) {
 #pragma unroll
-                for (int j = 0; j < C; ++j) {
-                    if (next_step) {
-                        phys::relax_cell(a.ph, a.eps, a2v[j], v[r][j], v[r][j], m1[j], m2[j], Tr[r][j], ar[r][j]);
-                        Ln[r][j] = law(Tr[r][j], ar[r][j], m1[j], m2[j]);
-                    } else if constexpr (kSH) {
-                        Ln[r][j] = law(v[r][j], a2v[j], m1[j], m2[j]);
-                    } else {
-                        Ln[r][j] = law(v[r][j], a2v[j], 0.0, 0.0);
-                    }
-                }
+                for (int r = 0; r < RW; ++r)
+#pragma unroll
+                    for (int j = 0; j < C; ++j)
+                        if (phys::is_mixed(a2v[r][j], a.eps))
+                            phys::relax_equal_pinf(a.ph, v[r][j], m1v[r][j], m2v[r][j], v[r][j], a2v[r][j]);
+            }
+            if constexpr (kSH) {
+#pragma unroll
+                for (int r = 0; r < RW; ++r)
+#pragma unroll
+                    for (int j = 0; j < C; ++j) Ln[r][j] = law(v[r][j], a2v[r][j], m1v[r][j], m2v[r][j]);
+            } else {
+                phys::lambda_rows(a.ph, v, a2v, Ln);
             }
             // the seam buffer not used by the last stage: its reads all
             // precede that stage's barrier
@@ -654,38 +738,45 @@ __global__ void __launch_bounds__(64 * NW, 4) k_tb2d(TBArgs<R> a) {
                 sh_lo[b2][wv][j][lane] = Ln[0][j];
                 sh_hi[b2][wv][j][lane] = Ln[RW - 1][j];
             }
+            double rcv[RW][C];
+#pragma unroll
+            for (int r = 0; r < RW; ++r)
+#pragma unroll
+                for (int j = 0; j < C; ++j) rcv[r][j] = row(a.rC, r)[xs[j]];
             __syncthreads();
             double Ldn[C], Lup[C];
 #pragma unroll
             for (int j = 0; j < C; ++j) {
-                Ldn[j] = wv > 0 ? sh_hi[b2][wv - 1][j][lane] : Ln[0][j];
-                Lup[j] = wv < WAVES - 1 ? sh_lo[b2][wv + 1][j][lane] : Ln[RW - 1][j];
+                Ldn[j] = wv > 0 ? sh_hi[b2][wv > 0 ? wv - 1 : 0][j][lane] : Ln[0][j];
+                Lup[j] = wv < WAVES - 1 ? sh_lo[b2][wv < WAVES - 1 ? wv + 1 : wv][j][lane] : Ln[RW - 1][j];
             }
             double bound = 0.0;
+            {
 #pragma unroll
-            for (int r = 0; r < RW; ++r)
+                for (int r = 0; r < RW; ++r)
 #pragma unroll
-                for (int j = 0; j < C; ++j) {
-                    const double Ll = left_of(Ln[r], j), Lr = right_of(Ln[r], j);
-                    const double Ld = r > 0 ? Ln[r - 1][j] : Ldn[j];
-                    const double Lu = r < RW - 1 ? Ln[r + 1][j] : Lup[j];
-                    const int y = yg0 + r;
-                    if (xo[j] && yout(r)) {
+                    for (int j = 0; j < C; ++j) {
+                        const double Ll = left_of(Ln[r], j), Lr = right_of(Ln[r], j);
+                        const double Ld = r > 0 ? Ln[r - 1][j] : Ldn[j];
+                        const double Lu = r < RW - 1 ? Ln[r + 1][j] : Lup[j];
+                        const int y = yg0 + r;
                         const bool fD = a.pery ? a.ny > 1 : y > 0;
                         const bool fU = a.pery ? a.ny > 1 : y < a.ny - 1;
-                        const int64_t o = (int64_t)y * a.nx + xg[j];
                         double d = 0.0;
-                        if (fL[j]) d += a.wx * fmean<double>(Ln[r][j], Ll, a.face);
-                        if (fR[j]) d += a.wx * fmean<double>(Ln[r][j], Lr, a.face);
-                        if (fD) d += a.wy * fmean<double>(Ln[r][j], Ld, a.face);
-                        if (fU) d += a.wy * fmean<double>(Ln[r][j], Lu, a.face);
-                        const double rc = a.rC[o];
-                        bound = fmax(bound, 2.0 * d * rc);
-                        a.Lam_next[o] = Ln[r][j];
-                        if (next_step) {
-                            a.Tn_next[o] = Tr[r][j];
-                            a.a2_next[o] = ar[r][j];
-                        }
+                        if (fL[j]) d += a.wx * fmean<double>(Ln[r][j], Ll, face);
+                        if (fR[j]) d += a.wx * fmean<double>(Ln[r][j], Lr, face);
+                        if (fD) d += a.wy * fmean<double>(Ln[r][j], Ld, face);
+                        if (fU) d += a.wy * fmean<double>(Ln[r][j], Lu, face);
+                        bound = fmax(bound, yo[r] && xo[j] ? 2.0 * d * rcv[r][j] : 0.0);
+                    }
+            }
+#pragma unroll
+            for (int r = 0; r < RW; ++r)
+                if (yo[r]) {
+                    put(a.Lam_next, r, Ln[r]);
+                    if (next_step) {
+                        put(a.Tn_next, r, v[r]);
+                        put(a.a2_next, r, a2v[r]);
                     }
                 }
 #pragma unroll
@@ -726,15 +817,9 @@ int launch_tb2d(hipStream_t s, const DevGrid& g, int face, const R* v, const R* 
     a.g64w[1] = g.w[1];
     a.stages = stages;
     a.sstride = sstride;
-    const bool tall = g.ny >= TALL_ROWS;
-    // two cells per lane (float stages only): a lane's pair must not
-    // straddle a periodic wrap
-    constexpr bool kWideOk = sizeof(R) == 4;
-    const bool wide = kWideOk && tall && g.nx >= WIDE_COLS && (g.nx % 2 == 0 || !g.per[0]);
-    const int kmax = tall ? KMAX_TB : KMAX_SHORT;
-    const int EXT_X = wide ? 128 : 64;
-    const int EXT_Y = wide ? 16 * (ROWS / 2) : (tall ? 16 : 8) * ROWS;
-    int K = count < kmax ? count : kmax;
+    const int K = count < KMAX_TB ? count : KMAX_TB;
+    const int shape = best_shape(g, K, nc ? K + 1 : K, sizeof(R) == 4);
+    const Shape& t = kShapeTab[shape];
     a.v = v;
     a.G = G;
     a.Lam = Lam;
@@ -749,14 +834,15 @@ int launch_tb2d(hipStream_t s, const DevGrid& g, int face, const R* v, const R* 
     a.pery = g.per[1];
     a.wx = (R)g.w[0];
     a.wy = (R)g.w[1];
+    a.fx = (R)(face == 1 ? g.w[0] : 0.5 * g.w[0]);
+    a.fy = (R)(face == 1 ? g.w[1] : 0.5 * g.w[1]);
     a.tau = (R)tau;
     a.taud = tau;
     a.K = K;
     a.H = nc ? K + 1 : K;
-    a.face = face;
-    a.hx = wide ? (a.H + 1) & ~1 : a.H;
-    a.ox = EXT_X - 2 * a.hx;
-    a.oy = EXT_Y - 2 * a.H;
+    a.hx = t.c == 2 ? (a.H + 1) & ~1 : a.H;
+    a.ox = t.ext_x() - 2 * a.hx;
+    a.oy = t.ext_y() - 2 * a.H;
     a.tiles_x = (g.nx + a.ox - 1) / a.ox;
     int tiles_y = (g.ny + a.oy - 1) / a.oy;
     for (int k = 0; k < K; ++k) {
@@ -765,34 +851,30 @@ int launch_tb2d(hipStream_t s, const DevGrid& g, int face, const R* v, const R* 
     }
     const dim3 grid((unsigned)(a.tiles_x * tiles_y));
     const bool sh = nc && nc->ph.spitzer;
-    auto go = [&](auto kern, int nw) { hipLaunchKernelGGL(kern, grid, dim3(64 * nw), 0, s, a); };
-    if (stages) {  // (no epilogue: the kept-stage launches of the adjoint's recompute)
-        if (tall) go(k_tb2d<R, 16, 1, true, false>, 16);
-        else go(k_tb2d<R, 8, 1, true, false>, 8);
-    } else if (sh) {
-        if constexpr (kWideOk) {
-            if (wide) {
-                go(k_tb2d<R, 16, 2, false, true>, 16);
-                return K;
-            }
+    auto go = [&](auto harm, auto keep, auto spitzer) {
+        constexpr bool kHarm = decltype(harm)::value, kKeep = decltype(keep)::value, kSH = decltype(spitzer)::value;
+        auto run = [&](auto kern) { hipLaunchKernelGGL(kern, grid, dim3(64 * NWAVES), 0, s, a); };
+        switch (shape) {
+            case S_WIDE: run(k_tb2d<R, NWAVES, 4, 2, kKeep, kSH, kHarm>); break;
+            case S_TALL: run(k_tb2d<R, NWAVES, 8, 1, kKeep, kSH, kHarm>); break;
+            case S_SQUARE: run(k_tb2d<R, NWAVES, 4, 1, kKeep, kSH, kHarm>); break;
+            default: run(k_tb2d<R, NWAVES, 2, 1, kKeep, kSH, kHarm>); break;
         }
-        if (tall) go(k_tb2d<R, 16, 1, false, true>, 16);
-        else go(k_tb2d<R, 8, 1, false, true>, 8);
-    } else {
-        if constexpr (kWideOk) {
-            if (wide) {
-                go(k_tb2d<R, 16, 2, false, false>, 16);
-                return K;
-            }
+    };
+    auto laws = [&](auto harm) {
+        if constexpr (sizeof(R) == 8) {  // kept stages (the adjoint's recompute): FP64, no epilogue
+            if (stages) return go(harm, std::true_type{}, std::false_type{});
         }
-        if (tall) go(k_tb2d<R, 16, 1, false, false>, 16);
-        else go(k_tb2d<R, 8, 1, false, false>, 8);
-    }
+        if (sh) go(harm, std::false_type{}, std::true_type{});
+        else go(harm, std::false_type{}, std::false_type{});
+    };
+    if (face == 1) laws(std::true_type{});
+    else laws(std::false_type{});
     return K;
 }
 
 bool use_tb2d(const DevGrid& g, int count) {
-    return g.nz == 1 && g.ny >= 8 * ROWS / 2 && count >= 2;
+    return g.nz == 1 && g.ny >= 32 && count >= 2;
 }
 
 StageParam one_stage(const Stages& st) {
@@ -819,13 +901,22 @@ int launch_sweeps64_keep(hipStream_t s, const DevGrid& g, int face, const double
     return -1;
 }
 
-int sweeps_per_launch(const DevGrid& g, int count) {
+int sweeps_per_launch(const DevGrid& g, int count, bool f32) {
     if (!use_tb2d(g, count)) return b3d_stages(g, count);
-    // as few launches as the tile allows, with equal stage counts: a launch
-    // of K stages recomputes a ring of width K, so even launches waste least
-    const int kmax = g.ny >= TALL_ROWS ? KMAX_TB : KMAX_SHORT;
-    const int launches = (count + kmax - 1) / kmax;
-    return (count + launches - 1) / launches;
+    // equal launches (a launch of K stages recomputes a ring of width K, so
+    // even launches waste least), as many as cost least
+    int best = 0;
+    double low = 0.0;
+    for (int n = (count + KMAX_TB - 1) / KMAX_TB; n <= count && (best == 0 || n <= best + 4); ++n) {
+        const int k = (count + n - 1) / n;
+        double cost;
+        if (best_shape(g, k, k + 1, f32, &cost) < 0) continue;
+        if (best == 0 || n * cost < low) {
+            best = n;
+            low = n * cost;
+        }
+    }
+    return (count + best - 1) / best;
 }
 
 int launch_sweeps64(hipStream_t s, const DevGrid& g, int face, const double* v, const double* rhs,
