@@ -1409,6 +1409,10 @@ bool step2d_ok(const tlim_ctx* c, const tlim_step_opts* o) {
     if (c->precision != TLIM_FP64 || o->cycle_mode || o->frozen_lambda || o->picard_tol > 0.0) return false;
     if (c->phase[0].pinf != c->phase[1].pinf) return false;
     const DevGrid g = dev_grid(c, kUnit);
+    // AUTO: on smaller grids a step with a readback per pass on smaller tiles
+    // is the faster one (512 x 300, three passes: about 130 us of launches and
+    // readbacks against 190 us; with Spitzer-Harm laws 180 against 263 us)
+    if (o->whole_step == TLIM_WHOLE_AUTO && !tlim::big_tiles2d(g)) return false;
     return fast_coeffs(c, g) && tlim::step2d_tiles(g) > 0;
 }
 

@@ -29,6 +29,11 @@ struct Stages {
 // f32: stages of the FP32 correction form.
 int sweeps_per_launch(const DevGrid& g, int count, bool f32 = false);
 
+// The grid's double launches run on the largest tiles (no CUs left idle on
+// them): where the whole-step kernel, whose tiles are always that large, can
+// compete with them.
+bool big_tiles2d(const DevGrid& g);
+
 // The next Picard pass's coefficients, built by the launch that reaches the
 // final stage when it can (blocked 2D launches): Lam = sum_k alpha_k
 // lambda_k(T^(it+1)) and the Gershgorin bound (max into the row lam), with

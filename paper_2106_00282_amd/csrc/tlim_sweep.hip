@@ -919,6 +919,12 @@ int sweeps_per_launch(const DevGrid& g, int count, bool f32) {
     return (count + best - 1) / best;
 }
 
+bool big_tiles2d(const DevGrid& g) {
+    if (!use_tb2d(g, 8)) return false;
+    const int shape = best_shape(g, 8, 9, false);
+    return shape == S_WIDE || shape == S_TALL;
+}
+
 int launch_sweeps64(hipStream_t s, const DevGrid& g, int face, const double* v, const double* rhs,
                     const double* Lam, const double* rC, double* out, Stages st, int count, bool last, double tau,
                     const double* Tit, PassSlots ps, const NextCoef* nc, bool* nc_done) {
