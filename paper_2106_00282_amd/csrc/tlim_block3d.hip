@@ -20,19 +20,23 @@
 // cells at the column's x and y edges go stale (they are written by the
 // neighbouring columns), and a chunk starts K planes early and ends K late.
 //
-// What bounds it: at 512^3 in float a launch of 3 stages takes 726 us, 4.5 TB/s
-// over the 23.5 B per cell it moves with the column halos (64 x 64 cells for
-// 58 x 58 results); one stage per launch took 549 us.  Per stage 549 -> 242 us
-// there, 77 -> 41 us at 256^3, in double 22 -> 13.5 us at 128^3 and 28 -> 11.7 us
-// at 150 x 131 x 97.  The registers of K stages set the rows per wave: 8 waves
-// (two per SIMD, 256 VGPRs each) of 8 float rows, or of 3 (K = 3) or 4 (K = 2)
-// double rows; one row more spills (K = 3: 726 -> 1352 us with 4 rows on 16
-// waves of 128 VGPRs, 40 -> 61 us at 128^3 in double with 4 rows).
+// What bounds it: a plane step's instructions and, on grids beyond the
+// caches, memory.  At 512^3 in float a launch of 4 stages takes 806 us (202 us
+// per stage; 549 us one stage per launch), at 256^3 113 us (28 against 77), and
+// a launch of 3 at 512^3 moves 3.9 GB at 5.6 TB/s (64 x 48 cells read for 58 x 42
+// results, in rows that do not start on a cache line).  In double a launch of
+// 3 stages takes 34 us at 128^3 (11 us per stage against 22) and 28 us at
+// 150 x 131 x 97 (9.4 against 28).  The registers of K stages set the rows per
+// wave: 8 waves of two per SIMD, 256 VGPRs each; one row more spills (4 stages
+// at 256^3: 113 -> 318 us).
 //
 // Arithmetic of a stage: with F_f = mean(Lambda_a, Lambda_b) (v_b - v_a) formed
 // once per face and shared by its two cells,
 //   out = c_m (G + tau b_m v + rC sum_d tau w_d (F_up - F_low)).
 #include <hip/hip_runtime.h>
+
+#include <type_traits>
+#include <utility>
 
 #include "tlim_device.h"
 #include "tlim_sweep.h"
@@ -45,7 +49,7 @@ using tb::fold;
 using tb::from_left;
 using tb::from_right;
 
-constexpr int KMAX3 = 3;
+constexpr int KMAX3 = 4;
 constexpr int kCUs = 256;
 
 template <typename R>
@@ -77,9 +81,30 @@ __device__ __forceinline__ R face_of(R a, R b) {
     else return s;
 }
 
-template <typename R, int K, int ROWS, int WAVES, bool kHarm>
+// f(0), f(1), ... with compile-time arguments.
+template <typename F, int... J>
+__device__ __forceinline__ void unroll(F&& f, std::integer_sequence<int, J...>) {
+    (f(std::integral_constant<int, J>{}), ...);
+}
+
+// What a launch does beside the stages themselves.
+enum B3Mode {
+    B3_PLAIN,
+    B3_FROM_G,  // the input is c_in G (v is not read)
+    B3_KEEP,    // every stage's result is kept
+    B3_REDUCE   // the pass reductions of the last stage's result
+};
+
+// A plane step executes a fixed number of instructions per wave, and with two
+// waves per SIMD these set its time as soon as the loads are ahead (1850 of
+// them took 4 us where the arithmetic is 540), so: each load and store is a
+// scalar plane pointer plus the row's 32-bit offset held in a register; planes
+// wrap by a counter; Lambda, 1/C and G of the waiting planes sit in rings of
+// K + 1 registers that the loads fill in place, indexed at compile time in a
+// plane loop unrolled K + 1 times, instead of being moved along.
+template <typename R, int K, int ROWS, int WAVES, bool kHarm, B3Mode kMode>
 __global__ void __launch_bounds__(64 * WAVES) k_b3d(B3Args<R> a) {
-    constexpr int RW = ROWS + 2;
+    constexpr int RW = ROWS + 2, U = K + 1;
     constexpr int OX = 64 - 2 * K, EXT_Y = WAVES * ROWS, OY = EXT_Y - 2 * K;
     // seam rows of the K stage inputs: [buffer][stage][wave][first / last row]
     __shared__ R sh[2][K][WAVES][2][64];
@@ -102,15 +127,13 @@ __global__ void __launch_bounds__(64 * WAVES) k_b3d(B3Args<R> a) {
         tbk[k] = (R)t;
         cmk[k] = (R)(1.0 / (1.0 + t));
     }
-    const bool from_g = a.v == nullptr;
-    const R vs = from_g ? (R)(1.0 / (1.0 + (a.lam ? a.tau * lamv * a.chat_in : a.tb_in))) : R(1);
-    const R* __restrict__ vin_p = from_g ? a.G : a.v;
+    const R vs = kMode == B3_FROM_G ? (R)(1.0 / (1.0 + (a.lam ? a.tau * lamv * a.chat_in : a.tb_in))) : R(1);
 
     const int tile = tb::xcd_block();
     const int tx = tile % a.tiles_x, rest = tile / a.tiles_x;
     const int ty = rest % a.tiles_y, tz = rest / a.tiles_y;
     const int xg = tx * OX - K + lane;
-    const unsigned xi = (unsigned)fold(xg, nx, a.perx);
+    const int xi = fold(xg, nx, a.perx);
     const int y0 = ty * OY - K + wv * ROWS;  // first own row
     const int z0 = tz * a.zc;
     const int z1 = z0 + a.zc < nz ? z0 + a.zc : nz;
@@ -124,47 +147,82 @@ __global__ void __launch_bounds__(64 * WAVES) k_b3d(B3Args<R> a) {
         const int y = y0 + r - 1;
         wyf[r] = (a.pery ? ny > 1 : (y >= 0 && y < ny - 1)) ? a.wy : R(0);
     }
-    const int64_t plane = (int64_t)nx * ny;
-    int rowoff[RW];  // wave-uniform offsets of rows -1 .. ROWS within a plane
+    const int zlo = a.perz ? -(1 << 30) : 0, zhi = a.perz ? (nz > 1 ? 1 << 30 : -(1 << 30)) : nz - 1;
+    unsigned rows_out = 0;  // output rows of this wave
 #pragma unroll
-    for (int r = 0; r < RW; ++r) rowoff[r] = fold(y0 - 1 + r, ny, a.pery) * nx;
-
-    R vc[K][ROWS];     // input of stage q + 1 on plane z - 1 - q
-    R fz[K][ROWS];     // its weighted flux through the face below that plane
-    R Lq[K + 1][RW];   // Lambda on planes z .. z - K
-    R rc[K][ROWS], Gq[K][ROWS];  // 1/C and G on planes z - 1 .. z - K
-    R nv[ROWS], nL[RW], nrc[ROWS], nG[ROWS];  // in flight: v, Lambda of plane z, 1/C and G of plane z - 1
-    auto load_vL = [&](int z) {
-        const int64_t pz = fold(z, nz, a.perz) * plane;
+    for (int r = 0; r < ROWS; ++r) {
+        const int row = wv * ROWS + r;
+        rows_out |= (unsigned)((row >= K) & (row < EXT_Y - K) & (y0 + r < ny)) << r;
+    }
+    // byte offsets of the lane's cells of rows -1 .. ROWS within a plane (the
+    // launcher keeps planes under 2 GiB)
+    const int64_t plane = (int64_t)nx * ny * (int64_t)sizeof(R);
+    unsigned off[RW];
 #pragma unroll
-        for (int r = 0; r < ROWS; ++r) nv[r] = (vin_p + (pz + rowoff[r + 1]))[xi];
-#pragma unroll
-        for (int r = 0; r < RW; ++r) nL[r] = (a.Lam + (pz + rowoff[r]))[xi];
+    for (int r = 0; r < RW; ++r) off[r] = (unsigned)(fold(y0 - 1 + r, ny, a.pery) * nx + xi) * (unsigned)sizeof(R);
+    auto at = [&](auto* base, unsigned o) -> auto& {
+        using T = std::remove_reference_t<decltype(*base)>;
+        using B = std::conditional_t<std::is_const_v<T>, const char, char>;
+        return *reinterpret_cast<T*>(reinterpret_cast<B*>(base) + o);
     };
-    auto load_cG = [&](int z) {
-        const int64_t pz = fold(z, nz, a.perz) * plane;
+    auto on_plane = [&](auto* f, int64_t pz) {  // f's plane at byte offset pz
+        using T = std::remove_reference_t<decltype(*f)>;
+        using B = std::conditional_t<std::is_const_v<T>, const char, char>;
+        return reinterpret_cast<T*>(reinterpret_cast<B*>(f) + pz);
+    };
+
+    R vc[K][ROWS];            // input of stage q + 1 on plane z - 1 - q
+    R fz[K][ROWS];            // its weighted flux through the face below that plane
+    R Lr[U][RW], nL[RW];      // Lambda: ring of planes z .. z - K, and plane z + 1 in flight
+    R rc[U][ROWS], Gq[U][ROWS];  // 1/C and G: ring of planes z (in flight) .. z - K
+    R nv[ROWS];               // v: plane z + 1 in flight
+    int zi = fold(z0 - K, nz, a.perz);  // folded index of the plane zv that was loaded last
+    int zv = z0 - K;
+    auto load_vL = [&](R (&vv)[ROWS], R (&LL)[RW]) {
+        const int64_t pz = (int64_t)zi * plane;
+        const R* fv = on_plane(kMode == B3_FROM_G ? a.G : a.v, pz);
+        const R* fL = on_plane(a.Lam, pz);
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) vv[r] = at(fv, off[r + 1]);
+#pragma unroll
+        for (int r = 0; r < RW; ++r) LL[r] = at(fL, off[r]);
+    };
+    auto load_cG = [&](R (&cc)[ROWS], R (&GG)[ROWS]) {
+        const int64_t pz = (int64_t)zi * plane;
+        const R* fc = on_plane(a.rC, pz);
+        const R* fG = on_plane(a.G, pz);
 #pragma unroll
         for (int r = 0; r < ROWS; ++r) {
-            nrc[r] = (a.rC + (pz + rowoff[r + 1]))[xi];
-            nG[r] = (a.G + (pz + rowoff[r + 1]))[xi];
+            cc[r] = at(fc, off[r + 1]);
+            GG[r] = at(fG, off[r + 1]);
         }
     };
-    const int zs = z0 - K;  // first plane
+    auto next_plane = [&]() {  // wraps on a periodic axis, stays within the grid at walls
+        ++zv;
+        if (a.perz) zi = zi + 1 == nz ? 0 : zi + 1;
+        else zi = zv < 0 ? 0 : (zv < nz ? zv : nz - 1);
+    };
 #pragma unroll
     for (int q = 0; q < K; ++q)
 #pragma unroll
-        for (int r = 0; r < ROWS; ++r) vc[q][r] = fz[q][r] = rc[q][r] = Gq[q][r] = R(0);
+        for (int r = 0; r < ROWS; ++r) vc[q][r] = fz[q][r] = R(0);
 #pragma unroll
-    for (int q = 0; q <= K; ++q)
+    for (int q = 0; q < U; ++q) {
 #pragma unroll
-        for (int r = 0; r < RW; ++r) Lq[q][r] = R(0);
-    load_vL(zs);
+        for (int r = 0; r < RW; ++r) Lr[q][r] = R(0);
 #pragma unroll
-    for (int r = 0; r < ROWS; ++r) vc[0][r] = vs * nv[r];
+        for (int r = 0; r < ROWS; ++r) rc[q][r] = Gq[q][r] = R(0);
+    }
+    // ring slot of plane zs + j: j % U.  Plane zs (slot 0) is the first input;
+    // plane zs + 1 is in flight when the loop begins.
+    load_vL(vc[0], Lr[0]);
+    load_cG(rc[0], Gq[0]);
+    next_plane();
+    load_vL(nv, nL);
+    if constexpr (kMode == B3_FROM_G) {
 #pragma unroll
-    for (int r = 0; r < RW; ++r) Lq[0][r] = nL[r];
-    load_vL(zs + 1);
-    load_cG(zs);
+        for (int r = 0; r < ROWS; ++r) vc[0][r] *= vs;
+    }
     const int wdn = wv > 0 ? wv - 1 : 0, wup = wv < WAVES - 1 ? wv + 1 : wv;
     auto publish = [&](int buf) {
 #pragma unroll
@@ -176,85 +234,90 @@ __global__ void __launch_bounds__(64 * WAVES) k_b3d(B3Args<R> a) {
     publish(0);
     double dmax = 0.0, tmax = 0.0, bad = 0.0;
     int buf = 0;
-    for (int z = zs + 1; z < z1 + K; ++z) {
-        // plane z has arrived: shift the waiting planes and start the next loads
-        R vin[ROWS];
+    const int ze = z1 + K;  // planes zs + 1 .. ze - 1 arrive in turn
+    // one plane step: plane z = zs + j has arrived (ring slot S = j % U)
+    auto step = [&](auto S_, int z) {
+        constexpr int S = decltype(S_)::value;
+        R nxt[ROWS];  // the stage's input on the plane above
 #pragma unroll
-        for (int r = 0; r < ROWS; ++r) vin[r] = vs * nv[r];
+        for (int r = 0; r < ROWS; ++r) nxt[r] = kMode == B3_FROM_G ? vs * nv[r] : nv[r];
 #pragma unroll
-        for (int q = K; q > 0; --q)
-#pragma unroll
-            for (int r = 0; r < RW; ++r) Lq[q][r] = Lq[q - 1][r];
-#pragma unroll
-        for (int r = 0; r < RW; ++r) Lq[0][r] = nL[r];
-#pragma unroll
-        for (int q = K - 1; q > 0; --q)
-#pragma unroll
-            for (int r = 0; r < ROWS; ++r) {
-                rc[q][r] = rc[q - 1][r];
-                Gq[q][r] = Gq[q - 1][r];
-            }
-#pragma unroll
-        for (int r = 0; r < ROWS; ++r) {
-            rc[0][r] = nrc[r];
-            Gq[0][r] = nG[r];
-        }
-        load_vL(z + 1);
-        load_cG(z);
+        for (int r = 0; r < RW; ++r) Lr[S][r] = nL[r];
+        load_cG(rc[S], Gq[S]);  // plane z
+        next_plane();
+        load_vL(nv, nL);  // plane z + 1
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-        R nxt[ROWS];  // the stage's input on the plane above
-#pragma unroll
-        for (int r = 0; r < ROWS; ++r) nxt[r] = vin[r];
 #pragma unroll
         for (int q = 0; q < K; ++q) {
-            const int p = z - 1 - q;  // this stage's plane
-            const R wzf = (a.perz ? nz > 1 : (p >= 0 && p < nz - 1)) ? a.wz : R(0);
+            const int p = z - 1 - q;  // this stage's plane, in slot P; the plane above in slot N
+            constexpr int UU = U;
+            const int P = (S + 2 * UU - 1 - q) % UU, N = (S + 2 * UU - q) % UU;
+            const R wzf = ((p >= zlo) & (p < zhi)) ? a.wz : R(0);
             const R vlo = sh[buf][q][wdn][1][lane], vhi = sh[buf][q][wup][0][lane];
-            R fy = wyf[0] * face_of<R, kHarm>(Lq[q + 1][0], Lq[q + 1][1]) * (vc[q][0] - vlo);
+            R fy = wyf[0] * face_of<R, kHarm>(Lr[P][0], Lr[P][1]) * (vc[q][0] - vlo);
             R res[ROWS];
 #pragma unroll
             for (int r = 0; r < ROWS; ++r) {
-                const R c = vc[q][r], La = Lq[q + 1][r + 1];
+                const R c = vc[q][r], La = Lr[P][r + 1];
                 const R up = r < ROWS - 1 ? vc[q][r < ROWS - 1 ? r + 1 : r] : vhi;
                 const R fx = wxr * face_of<R, kHarm>(La, from_right(La)) * (from_right(c) - c);
-                const R fyu = wyf[r + 1] * face_of<R, kHarm>(La, Lq[q + 1][r + 2]) * (up - c);
-                const R fzu = wzf * face_of<R, kHarm>(La, Lq[q][r + 1]) * (nxt[r] - c);
+                const R fyu = wyf[r + 1] * face_of<R, kHarm>(La, Lr[P][r + 2]) * (up - c);
+                const R fzu = wzf * face_of<R, kHarm>(La, Lr[N][r + 1]) * (nxt[r] - c);
                 const R acc = (fx - from_left(fx)) + (fyu - fy) + (fzu - fz[q][r]);
                 fy = fyu;
                 fz[q][r] = fzu;
-                res[r] = cmk[q] * (Gq[q][r] + tbk[q] * c + rc[q][r] * acc);
+                res[r] = cmk[q] * (Gq[P][r] + tbk[q] * c + rc[P][r] * acc);
+                // (the divisions of several rows interleaved would spill)
+                if constexpr (kHarm) __builtin_amdgcn_sched_barrier(0);
             }
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int r = 0; r < ROWS; ++r) {
                 vc[q][r] = nxt[r];  // next step's centre
                 nxt[r] = res[r];
             }
-            if (q < K - 1 ? a.stages != nullptr : true) {
-                if (p >= z0 && p < z1) {  // uniform
-                    R* dst = (q < K - 1 ? a.stages + (int64_t)(q + 1) * a.sstride : a.out) + p * plane;
+            if ((q == K - 1 || kMode == B3_KEEP) && p >= z0 && p < z1) {  // uniform
+                R* dst = on_plane(q < K - 1 ? a.stages + (int64_t)(q + 1) * a.sstride : a.out, p * plane);
+                if (xout) {
+#pragma unroll
+                    for (int r = 0; r < ROWS; ++r)
+                        if (rows_out >> r & 1u) at(dst, off[r + 1]) = res[r];
+                }
+                if constexpr (kMode == B3_REDUCE) {
+                    if (a.ps.dmax) {
+                        const double* tit = on_plane(a.Tit, p * plane);
+                        double t[ROWS];
+#pragma unroll
+                        for (int r = 0; r < ROWS; ++r) t[r] = at(tit, off[r + 1]);
+#pragma unroll
+                        for (int r = 0; r < ROWS; ++r)
+                            dmax = fmax(dmax, xout && (rows_out >> r & 1u) ? fabs((double)res[r] - t[r]) : 0.0);
+                    }
 #pragma unroll
                     for (int r = 0; r < ROWS; ++r) {
-                        const int row = wv * ROWS + r, y = y0 + r;
-                        if (row >= K && row < EXT_Y - K && y < ny && xout) {
-                            (dst + (int64_t)y * nx)[(unsigned)xg] = res[r];
-                            if (sizeof(R) == 8 && q == K - 1 && a.Tit) {
-                                const double tn = (double)res[r];
-                                if (a.ps.dmax)
-                                    dmax = fmax(dmax, fabs(tn - (a.Tit + (p * plane + (int64_t)y * nx))[(unsigned)xg]));
-                                tmax = fmax(tmax, fabs(tn));
-                                if (!(tn > 0.0) || isinf(tn)) bad += 1.0;
-                            }
-                        }
+                        const double tn = (double)res[r];
+                        const bool o = xout && (rows_out >> r & 1u);
+                        tmax = fmax(tmax, o ? fabs(tn) : 0.0);
+                        bad += o && (!(tn > 0.0) || isinf(tn)) ? 1.0 : 0.0;
                     }
                 }
             }
         }
         buf ^= 1;
         publish(buf);
+    };
+    // steps j = 1, 2, ...: slot j % U
+    for (int z = z0 - K + 1; z < ze; z += U) {
+        unroll(
+            [&](auto J) {
+                constexpr int j = decltype(J)::value;
+                if (z + j < ze) step(std::integral_constant<int, (1 + j) % U>{}, z + j);
+            },
+            std::make_integer_sequence<int, U>{});
     }
-    if (sizeof(R) == 8 && a.Tit) {
+    if constexpr (kMode == B3_REDUCE) {
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) {
             dmax = fmax(dmax, __shfl_xor(dmax, o, 64));
@@ -272,15 +335,22 @@ __global__ void __launch_bounds__(64 * WAVES) k_b3d(B3Args<R> a) {
 }
 
 // y rows per wave: what K stages' planes leave room for in the 256 VGPRs of
-// two waves per SIMD (one row more spills)
-template <typename R, int K>
+// two waves per SIMD (harmonic means take a few more registers)
+template <typename R, int K, bool kHarm>
 constexpr int b3_rows() {
-    return sizeof(R) == 4 ? 8 : (K == 3 ? 3 : 4);
+    if (sizeof(R) == 8) return (K == 3 ? 3 : 4) - (kHarm ? 1 : 0);
+    return (K == 4 ? 5 : K == 3 ? 6 : 8) - (kHarm ? (K == 4 ? 2 : 1) : 0);
 }
 
-template <typename R, int K>
-void launch_b3d_k(hipStream_t s, const DevGrid& g, int face, B3Args<R>& a) {
-    constexpr int rows = b3_rows<R, K>(), waves = 8;
+// stages per launch
+template <typename R>
+constexpr int b3_kmax() {
+    return sizeof(R) == 8 ? 3 : 4;
+}
+
+template <typename R, int K, bool kHarm>
+void launch_b3d_k(hipStream_t s, const DevGrid& g, B3Args<R>& a) {
+    constexpr int rows = b3_rows<R, K, kHarm>(), waves = 8;
     constexpr int OX = 64 - 2 * K, OY = rows * waves - 2 * K;
     a.tiles_x = (g.nx + OX - 1) / OX;
     a.tiles_y = (g.ny + OY - 1) / OY;
@@ -300,15 +370,26 @@ void launch_b3d_k(hipStream_t s, const DevGrid& g, int face, B3Args<R>& a) {
     }
     a.zc = zc;
     const dim3 grid((unsigned)(cols * ((g.nz + zc - 1) / zc))), block(64 * waves);
-    if (face == 1) hipLaunchKernelGGL((k_b3d<R, K, rows, waves, true>), grid, block, 0, s, a);
-    else hipLaunchKernelGGL((k_b3d<R, K, rows, waves, false>), grid, block, 0, s, a);
+    auto go = [&](auto mode) {
+        hipLaunchKernelGGL((k_b3d<R, K, rows, waves, kHarm, decltype(mode)::value>), grid, block, 0, s, a);
+    };
+    if constexpr (sizeof(R) == 8) {
+        if (a.stages) go(std::integral_constant<B3Mode, B3_KEEP>{});
+        else if (a.Tit) go(std::integral_constant<B3Mode, B3_REDUCE>{});
+        else go(std::integral_constant<B3Mode, B3_PLAIN>{});
+    } else {
+        if (!a.v) go(std::integral_constant<B3Mode, B3_FROM_G>{});
+        else go(std::integral_constant<B3Mode, B3_PLAIN>{});
+    }
 }
 
 }  // namespace
 
-int b3d_stages(const DevGrid& g, int count) {
-    if (!use_z3d(g)) return 1;
-    const int launches = (count + KMAX3 - 1) / KMAX3;
+int b3d_stages(const DevGrid& g, int count, bool f32) {
+    // (a plane's byte offsets fit 31 bits)
+    if (!use_z3d(g) || (int64_t)g.nx * g.ny >= ((int64_t)1 << 28)) return 1;
+    const int kmax = f32 ? b3_kmax<float>() : b3_kmax<double>();
+    const int launches = (count + kmax - 1) / kmax;
     return (count + launches - 1) / launches;
 }
 
@@ -344,8 +425,16 @@ void launch_b3d(hipStream_t s, const DevGrid& g, int face, const R* v, const R* 
     a.wx = (R)(half * tau * g.w[0]);
     a.wy = (R)(half * tau * g.w[1]);
     a.wz = (R)(half * tau * g.w[2]);
-    if (K == 3) launch_b3d_k<R, 3>(s, g, face, a);
-    else launch_b3d_k<R, 2>(s, g, face, a);
+    auto run = [&](auto harm) {
+        constexpr bool h = decltype(harm)::value;
+        if (K == 2) return launch_b3d_k<R, 2, h>(s, g, a);
+        if constexpr (b3_kmax<R>() >= 4) {
+            if (K == 4) return launch_b3d_k<R, 4, h>(s, g, a);
+        }
+        launch_b3d_k<R, 3, h>(s, g, a);
+    };
+    if (face == 1) run(std::true_type{});
+    else run(std::false_type{});
 }
 
 template void launch_b3d<double>(hipStream_t, const DevGrid&, int, const double*, const double*, const double*,

@@ -78,8 +78,8 @@ bool use_z3d(const DevGrid& g);
 template <typename R>
 void launch_z3d(hipStream_t s, const DevGrid& g, int face, const R* v, const R* G, const R* Lam, const R* rC, R* out,
                 StageParam sp, double tau, const double* Tit, PassSlots ps);
-// K = 2 or 3 stages on a 3D grid in one launch (tlim_block3d.hip), for grids
-// with use_z3d.  v == NULL: the input is the stage before the first from
+// K = 2 .. 3 (double) or 4 (float) stages on a 3D grid in one launch
+// (tlim_block3d.hip), as b3d_stages gives them.  v == NULL: the input is the stage before the first from
 // w = 0, c_in G (sp_in: that stage's parameter).  With Tit != NULL (FP64, the
 // last stage the final one) also the pass reductions.  With stages != NULL
 // the result of stage s < K goes to stages + s*sstride as well.
@@ -88,7 +88,7 @@ void launch_b3d(hipStream_t s, const DevGrid& g, int face, const R* v, const R* 
                 Stages st, int K, double tau, const double* Tit, PassSlots ps, R* stages = nullptr,
                 int64_t sstride = 0, StageParam sp_in = StageParam{nullptr, 0.0, 0.0});
 // Stages of the next 3D launch when `count` remain (1 where blocking does not apply).
-int b3d_stages(const DevGrid& g, int count);
+int b3d_stages(const DevGrid& g, int count, bool f32);
 // Reverse stages of the adjoint on 3D grids by z-marching waves (arithmetic
 // face means): psi_out = c_m (tb psi - tau rC A' psi) with the face gradient
 // and dL/dg accumulated in place into gLam and dgpsi (psi = C^-1 lambda;

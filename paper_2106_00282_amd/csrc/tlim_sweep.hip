@@ -893,7 +893,7 @@ int launch_sweeps64_keep(hipStream_t s, const DevGrid& g, int face, const double
     if (use_tb2d(g, count))
         return launch_tb2d<double>(s, g, face, v, rhs, Lam, rC, out, st, count, tau, nullptr, PassSlots{}, stages,
                                    sstride);
-    const int k = b3d_stages(g, count);
+    const int k = b3d_stages(g, count, false);
     if (k > 1) {
         launch_b3d<double>(s, g, face, v, rhs, Lam, rC, out, st, k, tau, nullptr, PassSlots{}, stages, sstride);
         return k;
@@ -902,7 +902,7 @@ int launch_sweeps64_keep(hipStream_t s, const DevGrid& g, int face, const double
 }
 
 int sweeps_per_launch(const DevGrid& g, int count, bool f32) {
-    if (!use_tb2d(g, count)) return b3d_stages(g, count);
+    if (!use_tb2d(g, count)) return b3d_stages(g, count, f32);
     // equal launches (a launch of K stages recomputes a ring of width K, so
     // even launches waste least), as many as cost least
     int best = 0;
@@ -935,7 +935,7 @@ int launch_sweeps64(hipStream_t s, const DevGrid& g, int face, const double* v, 
         return launch_tb2d<double>(s, g, face, v, rhs, Lam, rC, out, st, count, tau, last ? Tit : nullptr, ps,
                                    nullptr, 0, nullptr, nullptr, nullptr, with_nc ? nc : nullptr);
     }
-    if (const int k = b3d_stages(g, count); k > 1) {
+    if (const int k = b3d_stages(g, count, false); k > 1) {
         launch_b3d<double>(s, g, face, v, rhs, Lam, rC, out, st, k, tau, last ? Tit : nullptr, ps);
         return k;
     }
@@ -970,7 +970,7 @@ int launch_sweeps32(hipStream_t s, const DevGrid& g, int face, const float* w, c
     if (last) {
         if (use_z3d(g)) launch_z3d_final32(s, g, face, w, rhs, Lam32, rC, out64, tau, Tit, ps);
         else launch_final32(s, g, face, w, rhs, Lam32, rC, out64, tau, Tit, ps);
-    } else if (const int k = b3d_stages(g, count); k > 1) {
+    } else if (const int k = b3d_stages(g, count, true); k > 1) {
         launch_b3d<float>(s, g, face, w, qn, Lam32, rC32, out, st, k, tau, nullptr, PassSlots{});
         return k;
     } else if (use_z3d(g)) {
