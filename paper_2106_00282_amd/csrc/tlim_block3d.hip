@@ -21,14 +21,14 @@
 // neighbouring columns), and a chunk starts K planes early and ends K late.
 //
 // What bounds it: a plane step's instructions and, on grids beyond the
-// caches, memory.  At 512^3 in float a launch of 4 stages takes 806 us (202 us
-// per stage; 549 us one stage per launch), at 256^3 113 us (28 against 77), and
+// caches, memory.  At 512^3 in float a launch of 4 stages takes 780 us (195 us
+// per stage; 549 us one stage per launch), at 256^3 108 us (27 against 77), and
 // a launch of 3 at 512^3 moves 3.9 GB at 5.6 TB/s (64 x 48 cells read for 58 x 42
 // results, in rows that do not start on a cache line).  In double a launch of
-// 3 stages takes 34 us at 128^3 (11 us per stage against 22) and 28 us at
-// 150 x 131 x 97 (9.4 against 28).  The registers of K stages set the rows per
+// 3 stages takes 31 us at 128^3 (10.5 us per stage against 22) and 27 us at
+// 150 x 131 x 97 (9.1 against 28).  The registers of K stages set the rows per
 // wave: 8 waves of two per SIMD, 256 VGPRs each; one row more spills (4 stages
-// at 256^3: 113 -> 318 us).
+// at 256^3: 108 -> 153 us).
 //
 // Arithmetic of a stage: with F_f = mean(Lambda_a, Lambda_b) (v_b - v_a) formed
 // once per face and shared by its two cells,
@@ -81,27 +81,85 @@ __device__ __forceinline__ R face_of(R a, R b) {
     else return s;
 }
 
+// A plane of a field as a buffer (wave-uniform: four scalar registers): its
+// words are addressed by the lane's 32-bit byte offset alone, where a pointer
+// takes a register pair and an addition per access.  Offsets past the plane
+// read 0 and write nothing.
+template <typename T>
+struct Plane {
+    __amdgpu_buffer_rsrc_t r;
+    __device__ __forceinline__ Plane(T* f, int64_t pz, int bytes)
+        : r(__builtin_amdgcn_make_buffer_rsrc(
+              const_cast<char*>(reinterpret_cast<const char*>(f) + pz), 0, bytes, 0x00027000)) {}
+    __device__ __forceinline__ T get(unsigned o) const {
+        if constexpr (sizeof(T) == 8) {
+            const auto x = __builtin_amdgcn_raw_buffer_load_b64(r, o, 0, 0);
+            return __builtin_bit_cast(std::remove_const_t<T>, x);
+        } else {
+            const auto x = __builtin_amdgcn_raw_buffer_load_b32(r, o, 0, 0);
+            return __builtin_bit_cast(std::remove_const_t<T>, x);
+        }
+    }
+    __device__ __forceinline__ void put(unsigned o, T x) const {
+        if constexpr (sizeof(T) == 8)
+            __builtin_amdgcn_raw_buffer_store_b64(
+                __builtin_bit_cast(decltype(__builtin_amdgcn_raw_buffer_load_b64(r, 0, 0, 0)), x), r, o, 0, 0);
+        else
+            __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, x), r, o, 0, 0);
+    }
+};
+
+// Byte offset of cell (xg, y) within a plane (xi: xg folded into the grid).
+// Cells that no result of a K-stage launch depends on -- beyond a wall, or more
+// than K past the end of a periodic axis, where the last column of a grid
+// reaches -- get an offset past the plane: they are not read (128^3 with 60 of
+// 64 x cells per column: 140 instead of 192 x cells read per row).
+template <int K>
+__device__ __forceinline__ unsigned word_offset(int xg, int y, int xi, int nx, int ny, int perx, int pery,
+                                                unsigned size) {
+    const bool needed = (perx ? xg < nx + K : (xg >= 0) & (xg < nx)) && (pery ? y < ny + K : (y >= 0) & (y < ny));
+    return needed ? (unsigned)(fold(y, ny, pery) * nx + xi) * size : 0x80000000u;
+}
+
 // f(0), f(1), ... with compile-time arguments.
 template <typename F, int... J>
 __device__ __forceinline__ void unroll(F&& f, std::integer_sequence<int, J...>) {
     (f(std::integral_constant<int, J>{}), ...);
 }
 
+// step(slot, z) for z = zb .. ze - 1, the first in slot 1 of a ring of U: whole
+// periods without a test between the steps (one would pin every register of
+// the rings and cost a move for each of them per step), then what is left.
+template <int U, typename F>
+__device__ __forceinline__ void run_steps(int zb, int ze, F&& step) {
+    int z = zb;
+    for (; z + U <= ze; z += U)
+        unroll([&](auto J) { step(std::integral_constant<int, (1 + decltype(J)::value) % U>{}, z + decltype(J)::value); },
+               std::make_integer_sequence<int, U>{});
+    unroll(
+        [&](auto J) {
+            if (z + decltype(J)::value < ze)
+                step(std::integral_constant<int, (1 + decltype(J)::value) % U>{}, z + decltype(J)::value);
+        },
+        std::make_integer_sequence<int, U - 1>{});
+}
+
 // What a launch does beside the stages themselves.
 enum B3Mode {
     B3_PLAIN,
     B3_FROM_G,  // the input is c_in G (v is not read)
-    B3_KEEP,    // every stage's result is kept
+    B3_KEEP,    // every stage's result is kept (stages set), or the same arithmetic without
     B3_REDUCE   // the pass reductions of the last stage's result
 };
 
 // A plane step executes a fixed number of instructions per wave, and with two
-// waves per SIMD these set its time as soon as the loads are ahead (1850 of
-// them took 4 us where the arithmetic is 540), so: each load and store is a
-// scalar plane pointer plus the row's 32-bit offset held in a register; planes
-// wrap by a counter; Lambda, 1/C and G of the waiting planes sit in rings of
-// K + 1 registers that the loads fill in place, indexed at compile time in a
-// plane loop unrolled K + 1 times, instead of being moved along.
+// waves per SIMD these set its time as soon as the loads are ahead (the first
+// form of this kernel ran 1850 of them in 4 us; the arithmetic of 24 cell
+// stages is 540), so: words are addressed through plane buffers, planes wrap by
+// a counter, and Lambda, 1/C and G of the waiting planes sit in rings of K + 1
+// registers that the loads fill in place, indexed at compile time in a plane
+// loop unrolled K + 1 times, instead of being moved along (22 instructions per
+// cell and stage, 16 of them arithmetic).
 template <typename R, int K, int ROWS, int WAVES, bool kHarm, B3Mode kMode>
 __global__ void __launch_bounds__(64 * WAVES) k_b3d(B3Args<R> a) {
     constexpr int RW = ROWS + 2, U = K + 1;
@@ -154,23 +212,11 @@ __global__ void __launch_bounds__(64 * WAVES) k_b3d(B3Args<R> a) {
         const int row = wv * ROWS + r;
         rows_out |= (unsigned)((row >= K) & (row < EXT_Y - K) & (y0 + r < ny)) << r;
     }
-    // byte offsets of the lane's cells of rows -1 .. ROWS within a plane (the
-    // launcher keeps planes under 2 GiB)
+    // byte offsets of the lane's cells of rows -1 .. ROWS within a plane
     const int64_t plane = (int64_t)nx * ny * (int64_t)sizeof(R);
     unsigned off[RW];
 #pragma unroll
-    for (int r = 0; r < RW; ++r) off[r] = (unsigned)(fold(y0 - 1 + r, ny, a.pery) * nx + xi) * (unsigned)sizeof(R);
-    auto at = [&](auto* base, unsigned o) -> auto& {
-        using T = std::remove_reference_t<decltype(*base)>;
-        using B = std::conditional_t<std::is_const_v<T>, const char, char>;
-        return *reinterpret_cast<T*>(reinterpret_cast<B*>(base) + o);
-    };
-    auto on_plane = [&](auto* f, int64_t pz) {  // f's plane at byte offset pz
-        using T = std::remove_reference_t<decltype(*f)>;
-        using B = std::conditional_t<std::is_const_v<T>, const char, char>;
-        return reinterpret_cast<T*>(reinterpret_cast<B*>(f) + pz);
-    };
-
+    for (int r = 0; r < RW; ++r) off[r] = word_offset<K>(xg, y0 - 1 + r, xi, nx, ny, a.perx, a.pery, sizeof(R));
     R vc[K][ROWS];            // input of stage q + 1 on plane z - 1 - q
     R fz[K][ROWS];            // its weighted flux through the face below that plane
     R Lr[U][RW], nL[RW];      // Lambda: ring of planes z .. z - K, and plane z + 1 in flight
@@ -180,21 +226,21 @@ __global__ void __launch_bounds__(64 * WAVES) k_b3d(B3Args<R> a) {
     int zv = z0 - K;
     auto load_vL = [&](R (&vv)[ROWS], R (&LL)[RW]) {
         const int64_t pz = (int64_t)zi * plane;
-        const R* fv = on_plane(kMode == B3_FROM_G ? a.G : a.v, pz);
-        const R* fL = on_plane(a.Lam, pz);
+        const Plane<const R> fv(kMode == B3_FROM_G ? a.G : a.v, pz, (int)plane);
+        const Plane<const R> fL(a.Lam, pz, (int)plane);
 #pragma unroll
-        for (int r = 0; r < ROWS; ++r) vv[r] = at(fv, off[r + 1]);
+        for (int r = 0; r < ROWS; ++r) vv[r] = fv.get(off[r + 1]);
 #pragma unroll
-        for (int r = 0; r < RW; ++r) LL[r] = at(fL, off[r]);
+        for (int r = 0; r < RW; ++r) LL[r] = fL.get(off[r]);
     };
     auto load_cG = [&](R (&cc)[ROWS], R (&GG)[ROWS]) {
         const int64_t pz = (int64_t)zi * plane;
-        const R* fc = on_plane(a.rC, pz);
-        const R* fG = on_plane(a.G, pz);
+        const Plane<const R> fc(a.rC, pz, (int)plane);
+        const Plane<const R> fG(a.G, pz, (int)plane);
 #pragma unroll
         for (int r = 0; r < ROWS; ++r) {
-            cc[r] = at(fc, off[r + 1]);
-            GG[r] = at(fG, off[r + 1]);
+            cc[r] = fc.get(off[r + 1]);
+            GG[r] = fG.get(off[r + 1]);
         }
     };
     auto next_plane = [&]() {  // wraps on a periodic axis, stays within the grid at walls
@@ -278,19 +324,19 @@ __global__ void __launch_bounds__(64 * WAVES) k_b3d(B3Args<R> a) {
                 vc[q][r] = nxt[r];  // next step's centre
                 nxt[r] = res[r];
             }
-            if ((q == K - 1 || kMode == B3_KEEP) && p >= z0 && p < z1) {  // uniform
-                R* dst = on_plane(q < K - 1 ? a.stages + (int64_t)(q + 1) * a.sstride : a.out, p * plane);
+            if ((q == K - 1 || (kMode == B3_KEEP && a.stages)) && p >= z0 && p < z1) {  // uniform
+                const Plane<R> dst(q < K - 1 ? a.stages + (int64_t)(q + 1) * a.sstride : a.out, p * plane, (int)plane);
                 if (xout) {
 #pragma unroll
                     for (int r = 0; r < ROWS; ++r)
-                        if (rows_out >> r & 1u) at(dst, off[r + 1]) = res[r];
+                        if (rows_out >> r & 1u) dst.put(off[r + 1], res[r]);
                 }
                 if constexpr (kMode == B3_REDUCE) {
                     if (a.ps.dmax) {
-                        const double* tit = on_plane(a.Tit, p * plane);
+                        const Plane<const double> tit(a.Tit, p * plane, (int)plane);
                         double t[ROWS];
 #pragma unroll
-                        for (int r = 0; r < ROWS; ++r) t[r] = at(tit, off[r + 1]);
+                        for (int r = 0; r < ROWS; ++r) t[r] = tit.get(off[r + 1]);
 #pragma unroll
                         for (int r = 0; r < ROWS; ++r)
                             dmax = fmax(dmax, xout && (rows_out >> r & 1u) ? fabs((double)res[r] - t[r]) : 0.0);
@@ -309,14 +355,7 @@ __global__ void __launch_bounds__(64 * WAVES) k_b3d(B3Args<R> a) {
         publish(buf);
     };
     // steps j = 1, 2, ...: slot j % U
-    for (int z = z0 - K + 1; z < ze; z += U) {
-        unroll(
-            [&](auto J) {
-                constexpr int j = decltype(J)::value;
-                if (z + j < ze) step(std::integral_constant<int, (1 + j) % U>{}, z + j);
-            },
-            std::make_integer_sequence<int, U>{});
-    }
+    run_steps<U>(z0 - K + 1, ze, step);
     if constexpr (kMode == B3_REDUCE) {
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) {
@@ -339,7 +378,7 @@ __global__ void __launch_bounds__(64 * WAVES) k_b3d(B3Args<R> a) {
 template <typename R, int K, bool kHarm>
 constexpr int b3_rows() {
     if (sizeof(R) == 8) return (K == 3 ? 3 : 4) - (kHarm ? 1 : 0);
-    return (K == 4 ? 5 : K == 3 ? 6 : 8) - (kHarm ? (K == 4 ? 2 : 1) : 0);
+    return (K == 4 ? 5 : K == 3 ? 6 : 8) - (kHarm ? (K >= 3 ? 2 : 1) : 0);
 }
 
 // stages per launch
@@ -348,15 +387,13 @@ constexpr int b3_kmax() {
     return sizeof(R) == 8 ? 3 : 4;
 }
 
-template <typename R, int K, bool kHarm>
-void launch_b3d_k(hipStream_t s, const DevGrid& g, B3Args<R>& a) {
-    constexpr int rows = b3_rows<R, K, kHarm>(), waves = 8;
-    constexpr int OX = 64 - 2 * K, OY = rows * waves - 2 * K;
-    a.tiles_x = (g.nx + OX - 1) / OX;
-    a.tiles_y = (g.ny + OY - 1) / OY;
-    // z chunks: one workgroup per CU at a time, each walking its chunk and
-    // 2K planes more; the count with the fewest planes walked in turn
-    const int64_t cols = (int64_t)a.tiles_x * a.tiles_y;
+// Columns of ox x oy results and the z chunks of a launch of K stages: one
+// workgroup per CU at a time, each walking its chunk and 2K planes more; the
+// count of chunks with the fewest planes walked in turn.
+int z_chunks(const DevGrid& g, int ox, int oy, int K, int& tiles_x, int& tiles_y) {
+    tiles_x = (g.nx + ox - 1) / ox;
+    tiles_y = (g.ny + oy - 1) / oy;
+    const int64_t cols = (int64_t)tiles_x * tiles_y;
     int64_t best = 0;
     int zc = g.nz;
     for (int n = 1; n <= g.nz && n <= 4 * kCUs; ++n) {
@@ -368,13 +405,23 @@ void launch_b3d_k(hipStream_t s, const DevGrid& g, B3Args<R>& a) {
             zc = c;
         }
     }
-    a.zc = zc;
-    const dim3 grid((unsigned)(cols * ((g.nz + zc - 1) / zc))), block(64 * waves);
+    return zc;
+}
+
+// (a plane's byte offsets fit 31 bits)
+bool b3d_applies(const DevGrid& g) { return use_z3d(g) && (int64_t)g.nx * g.ny < ((int64_t)1 << 28); }
+
+template <typename R, int K, bool kHarm>
+void launch_b3d_k(hipStream_t s, const DevGrid& g, B3Args<R>& a, bool keep) {
+    constexpr int rows = b3_rows<R, K, kHarm>(), waves = 8;
+    a.zc = z_chunks(g, 64 - 2 * K, rows * waves - 2 * K, K, a.tiles_x, a.tiles_y);
+    const int64_t wg = (int64_t)a.tiles_x * a.tiles_y * ((g.nz + a.zc - 1) / a.zc);
+    const dim3 grid((unsigned)wg), block(64 * waves);
     auto go = [&](auto mode) {
         hipLaunchKernelGGL((k_b3d<R, K, rows, waves, kHarm, decltype(mode)::value>), grid, block, 0, s, a);
     };
     if constexpr (sizeof(R) == 8) {
-        if (a.stages) go(std::integral_constant<B3Mode, B3_KEEP>{});
+        if (keep) go(std::integral_constant<B3Mode, B3_KEEP>{});
         else if (a.Tit) go(std::integral_constant<B3Mode, B3_REDUCE>{});
         else go(std::integral_constant<B3Mode, B3_PLAIN>{});
     } else {
@@ -386,8 +433,7 @@ void launch_b3d_k(hipStream_t s, const DevGrid& g, B3Args<R>& a) {
 }  // namespace
 
 int b3d_stages(const DevGrid& g, int count, bool f32) {
-    // (a plane's byte offsets fit 31 bits)
-    if (!use_z3d(g) || (int64_t)g.nx * g.ny >= ((int64_t)1 << 28)) return 1;
+    if (!b3d_applies(g)) return 1;
     const int kmax = f32 ? b3_kmax<float>() : b3_kmax<double>();
     const int launches = (count + kmax - 1) / kmax;
     return (count + launches - 1) / launches;
@@ -395,8 +441,8 @@ int b3d_stages(const DevGrid& g, int count, bool f32) {
 
 template <typename R>
 void launch_b3d(hipStream_t s, const DevGrid& g, int face, const R* v, const R* G, const R* Lam, const R* rC, R* out,
-                Stages st, int K, double tau, const double* Tit, PassSlots ps, R* stages, int64_t sstride,
-                StageParam sp_in) {
+                Stages st, int K, double tau, const double* Tit, PassSlots ps, StageParam sp_in, bool keep, R* stages,
+                int64_t sstride) {
     B3Args<R> a{};
     a.v = v;
     a.G = G;
@@ -427,21 +473,317 @@ void launch_b3d(hipStream_t s, const DevGrid& g, int face, const R* v, const R* 
     a.wz = (R)(half * tau * g.w[2]);
     auto run = [&](auto harm) {
         constexpr bool h = decltype(harm)::value;
-        if (K == 2) return launch_b3d_k<R, 2, h>(s, g, a);
+        if (K == 2) return launch_b3d_k<R, 2, h>(s, g, a, keep);
         if constexpr (b3_kmax<R>() >= 4) {
-            if (K == 4) return launch_b3d_k<R, 4, h>(s, g, a);
+            if (K == 4) return launch_b3d_k<R, 4, h>(s, g, a, keep);
         }
-        launch_b3d_k<R, 3, h>(s, g, a);
+        launch_b3d_k<R, 3, h>(s, g, a, keep);
     };
     if (face == 1) run(std::true_type{});
     else run(std::false_type{});
 }
 
 template void launch_b3d<double>(hipStream_t, const DevGrid&, int, const double*, const double*, const double*,
-                                 const double*, double*, Stages, int, double, const double*, PassSlots, double*,
-                                 int64_t, StageParam);
+                                 const double*, double*, Stages, int, double, const double*, PassSlots, StageParam,
+                                 bool, double*, int64_t);
 template void launch_b3d<float>(hipStream_t, const DevGrid&, int, const float*, const float*, const float*,
-                                const float*, float*, Stages, int, double, const double*, PassSlots, float*, int64_t,
-                                StageParam);
+                                const float*, float*, Stages, int, double, const double*, PassSlots, StageParam,
+                                bool, float*, int64_t);
+
+}  // namespace tlim
+
+// ------------------------------------------------------------------ adjoint
+
+namespace tlim {
+
+namespace {
+
+// Reverse stages of the LIM adjoint on 3D grids in psi = C^-1 lambda form
+// (arithmetic face means), K = 1 or 2 per launch, along the same z-march:
+//   psi^(m-1) = c_m (tau b_m psi^(m) - tau rC sum_f w_f Lambda_f (psi_a - psi_b)),
+//   dgpsi += c_m psi^(m)_a,
+//   gLam  += c_m sum_f (tau w_f / 2) (v_b - v_a)^(m-1) (psi_a - psi_b)^(m).
+// With e_f = (tau w_f / 2)(psi_b - psi_a) formed once per face, both sums of a
+// face follow from it: (Lambda_a + Lambda_b) e_f for psi and (v_b - v_a) e_f for
+// gLam, shared by the face's two cells.  The sums dgpsi and gLam of a plane
+// wait in registers from one stage to the next.
+// Per cell two stages read psi, Lambda, 1/C, both sums and two stored iterates
+// and write psi and both sums: 80 B against 144 B for two launches of one
+// stage.  At 128^3 a launch of two stages takes 53 us (one stage per launch by
+// waves of two rows, each with its own windows: 37 us), and waits for issue and
+// for memory in about equal parts; registers hold two rows per wave for K = 2
+// (three spill).
+struct A3Args {
+    const double* psi;
+    const double* v[2];  // v^(m-1) of the launch's stages, in the order they are reversed
+    const double* Lam;
+    const double* rC;
+    double* psi_out;
+    double* dgpsi;
+    double* gLam;
+    double cm[2], tb[2];
+    int nx, ny, nz, perx, pery, perz;
+    double hx, hy, hz;  // tau w / 2
+    int tiles_x, tiles_y, zc;
+};
+
+template <int K, int ROWS, bool kAcc>
+__global__ void __launch_bounds__(512) k_adj_b3d(A3Args a) {
+    constexpr int WAVES = 8, RW = ROWS + 2, U = K + 1;
+    constexpr int OX = 64 - 2 * K, EXT_Y = WAVES * ROWS, OY = EXT_Y - 2 * K;
+    // seam rows of the stages' psi and v: [buffer][stage][psi, v][wave][first / last row]
+    __shared__ double sh[2][K][2][WAVES][2][64];
+    const int lane = threadIdx.x & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int nx = a.nx, ny = a.ny, nz = a.nz;
+    const int tile = tb::xcd_block();
+    const int tx = tile % a.tiles_x, rest = tile / a.tiles_x;
+    const int ty = rest % a.tiles_y, tz = rest / a.tiles_y;
+    const int xg = tx * OX - K + lane;
+    const int xi = fold(xg, nx, a.perx);
+    const int y0 = ty * OY - K + wv * ROWS;
+    const int z0 = tz * a.zc;
+    const int z1 = z0 + a.zc < nz ? z0 + a.zc : nz;
+    const bool xout = lane >= K && lane < 64 - K && xg < nx;
+    const double hxr = (a.perx ? nx > 1 : (xg >= 0 && xg < nx - 1)) ? a.hx : 0.0;
+    double hyf[ROWS + 1];
+#pragma unroll
+    for (int r = 0; r <= ROWS; ++r) {
+        const int y = y0 + r - 1;
+        hyf[r] = (a.pery ? ny > 1 : (y >= 0 && y < ny - 1)) ? a.hy : 0.0;
+    }
+    const int zlo = a.perz ? -(1 << 30) : 0, zhi = a.perz ? (nz > 1 ? 1 << 30 : -(1 << 30)) : nz - 1;
+    unsigned rows_out = 0;
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) {
+        const int row = wv * ROWS + r;
+        rows_out |= (unsigned)((row >= K) & (row < EXT_Y - K) & (y0 + r < ny)) << r;
+    }
+    const int64_t plane = (int64_t)nx * ny * 8;
+    unsigned off[RW];
+#pragma unroll
+    for (int r = 0; r < RW; ++r) off[r] = word_offset<K>(xg, y0 - 1 + r, xi, nx, ny, a.perx, a.pery, 8);
+
+    double pc[K][ROWS], fz[K][ROWS], gz[K][ROWS];  // stage q + 1 on plane z - 1 - q: psi, face sums below
+    double va[K][ROWS], vb[K][ROWS], nv[K][ROWS];  // its v on that plane, the one above, and the next in flight
+    double Lr[U][RW], nL[RW];                      // Lambda: planes z .. z - K, and z + 1 in flight
+    double rc[U][ROWS];                            // 1/C: planes z (in flight) .. z - K
+    double np[ROWS], nd[ROWS], ng[ROWS];           // in flight: psi of z + 1, the sums of z
+    double ds[K][ROWS], gs[K][ROWS];               // the sums before stage q + 1 on its plane
+    int zi = fold(z0 - K, nz, a.perz), zv = z0 - K;  // plane zv (folded zi) was loaded last
+    auto load_a = [&]() {  // plane zv: psi, Lambda, v of the first stage
+        const int64_t pz = (int64_t)zi * plane;
+        const Plane<const double> fp(a.psi, pz, (int)plane), fv(a.v[0], pz, (int)plane), fL(a.Lam, pz, (int)plane);
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) {
+            np[r] = fp.get(off[r + 1]);
+            nv[0][r] = fv.get(off[r + 1]);
+        }
+#pragma unroll
+        for (int r = 0; r < RW; ++r) nL[r] = fL.get(off[r]);
+    };
+    auto load_b = [&](double (&cc)[ROWS]) {  // plane zv: 1/C, the sums, v of the second stage
+        const int64_t pz = (int64_t)zi * plane;
+        const Plane<const double> fc(a.rC, pz, (int)plane);
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) cc[r] = fc.get(off[r + 1]);
+        if constexpr (K == 2) {
+            const Plane<const double> fv(a.v[1], pz, (int)plane);
+#pragma unroll
+            for (int r = 0; r < ROWS; ++r) nv[1][r] = fv.get(off[r + 1]);
+        }
+        if constexpr (kAcc) {
+            const Plane<const double> fd(a.dgpsi, pz, (int)plane), fg(a.gLam, pz, (int)plane);
+#pragma unroll
+            for (int r = 0; r < ROWS; ++r) {
+                nd[r] = fd.get(off[r + 1]);
+                ng[r] = fg.get(off[r + 1]);
+            }
+        }
+    };
+    auto next_plane = [&]() {
+        ++zv;
+        if (a.perz) zi = zi + 1 == nz ? 0 : zi + 1;
+        else zi = zv < 0 ? 0 : (zv < nz ? zv : nz - 1);
+    };
+#pragma unroll
+    for (int q = 0; q < K; ++q)
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r)
+            pc[q][r] = fz[q][r] = gz[q][r] = va[q][r] = vb[q][r] = nv[q][r] = ds[q][r] = gs[q][r] = nd[r] = ng[r] = 0.0;
+#pragma unroll
+    for (int q = 0; q < U; ++q) {
+#pragma unroll
+        for (int r = 0; r < RW; ++r) Lr[q][r] = 0.0;
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) rc[q][r] = 0.0;
+    }
+    load_a();
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) {
+        pc[0][r] = np[r];
+        va[0][r] = nv[0][r];
+    }
+#pragma unroll
+    for (int r = 0; r < RW; ++r) Lr[0][r] = nL[r];
+    load_b(rc[0]);
+    next_plane();
+    load_a();
+    const int wdn = wv > 0 ? wv - 1 : 0, wup = wv < WAVES - 1 ? wv + 1 : wv;
+    auto publish = [&](int buf) {
+#pragma unroll
+        for (int q = 0; q < K; ++q) {
+            sh[buf][q][0][wv][0][lane] = pc[q][0];
+            sh[buf][q][0][wv][1][lane] = pc[q][ROWS - 1];
+            sh[buf][q][1][wv][0][lane] = va[q][0];
+            sh[buf][q][1][wv][1][lane] = va[q][ROWS - 1];
+        }
+    };
+    publish(0);
+    int buf = 0;
+    const int ze = z1 + K;
+    auto step = [&](auto S_, int z) {
+        constexpr int S = decltype(S_)::value;
+        // plane z has arrived (psi, Lambda and the first stage's v), and plane
+        // z - 1 of the rest
+        double nxt[ROWS];
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) {
+            nxt[r] = np[r];
+            ds[0][r] = nd[r];
+            gs[0][r] = ng[r];
+        }
+#pragma unroll
+        for (int q = 0; q < K; ++q)
+#pragma unroll
+            for (int r = 0; r < ROWS; ++r) vb[q][r] = nv[q][r];
+#pragma unroll
+        for (int r = 0; r < RW; ++r) Lr[S][r] = nL[r];
+        load_b(rc[S]);
+        next_plane();
+        load_a();
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+        double dn[K][ROWS], gn[K][ROWS];  // the sums after each stage
+#pragma unroll
+        for (int q = 0; q < K; ++q) {
+            const int p = z - 1 - q;
+            constexpr int UU = U;
+            const int P = (S + 2 * UU - 1 - q) % UU, N = (S + 2 * UU - q) % UU;
+            const double hzf = ((p >= zlo) & (p < zhi)) ? a.hz : 0.0;
+            const double plo = sh[buf][q][0][wdn][1][lane], phi = sh[buf][q][0][wup][0][lane];
+            const double vlo = sh[buf][q][1][wdn][1][lane], vhi = sh[buf][q][1][wup][0][lane];
+            double ed = hyf[0] * (pc[q][0] - plo);
+            double fy = (Lr[P][0] + Lr[P][1]) * ed, gy = (va[q][0] - vlo) * ed;
+            double res[ROWS];
+#pragma unroll
+            for (int r = 0; r < ROWS; ++r) {
+                const double c = pc[q][r], v = va[q][r], La = Lr[P][r + 1];
+                const double up = r < ROWS - 1 ? pc[q][r < ROWS - 1 ? r + 1 : r] : phi;
+                const double vu = r < ROWS - 1 ? va[q][r < ROWS - 1 ? r + 1 : r] : vhi;
+                const double ex = hxr * (from_right(c) - c);
+                const double fx = (La + from_right(La)) * ex, gx = (from_right(v) - v) * ex;
+                const double ey = hyf[r + 1] * (up - c);
+                const double fyu = (La + Lr[P][r + 2]) * ey, gyu = (vu - v) * ey;
+                const double ez = hzf * (nxt[r] - c);
+                const double fzu = (La + Lr[N][r + 1]) * ez, gzu = (vb[q][r] - v) * ez;
+                const double acc = (fx - from_left(fx)) + (fyu - fy) + (fzu - fz[q][r]);
+                const double g = (gx + from_left(gx)) + (gyu + gy) + (gzu + gz[q][r]);
+                fy = fyu;
+                gy = gyu;
+                fz[q][r] = fzu;
+                gz[q][r] = gzu;
+                dn[q][r] = ds[q][r] + a.cm[q] * c;
+                gn[q][r] = gs[q][r] - a.cm[q] * g;
+                res[r] = a.cm[q] * (a.tb[q] * c + rc[P][r] * acc);
+                __builtin_amdgcn_sched_barrier(0);  // (rows interleaved would spill)
+            }
+#pragma unroll
+            for (int r = 0; r < ROWS; ++r) {
+                pc[q][r] = nxt[r];
+                nxt[r] = res[r];
+                va[q][r] = vb[q][r];
+            }
+            if (q == K - 1 && p >= z0 && p < z1) {  // uniform
+                const Plane<double> op(a.psi_out, p * plane, (int)plane), od(a.dgpsi, p * plane, (int)plane),
+                    og(a.gLam, p * plane, (int)plane);
+                if (xout) {
+#pragma unroll
+                    for (int r = 0; r < ROWS; ++r)
+                        if (rows_out >> r & 1u) {
+                            op.put(off[r + 1], res[r]);
+                            od.put(off[r + 1], dn[q][r]);
+                            og.put(off[r + 1], gn[q][r]);
+                        }
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        // the sums of a plane wait for the next stage's step
+#pragma unroll
+        for (int q = 1; q < K; ++q)
+#pragma unroll
+            for (int r = 0; r < ROWS; ++r) {
+                ds[q][r] = dn[q - 1][r];
+                gs[q][r] = gn[q - 1][r];
+            }
+        buf ^= 1;
+        publish(buf);
+    };
+    run_steps<U>(z0 - K + 1, ze, step);
+}
+
+template <int K>
+void launch_adj_b3d_k(hipStream_t s, const DevGrid& g, A3Args& a, bool accumulate) {
+    constexpr int rows = K == 2 ? 2 : 4, waves = 8;
+    a.zc = z_chunks(g, 64 - 2 * K, rows * waves - 2 * K, K, a.tiles_x, a.tiles_y);
+    const int64_t wg = (int64_t)a.tiles_x * a.tiles_y * ((g.nz + a.zc - 1) / a.zc);
+    if (accumulate) hipLaunchKernelGGL((k_adj_b3d<K, rows, true>), dim3((unsigned)wg), dim3(64 * waves), 0, s, a);
+    else hipLaunchKernelGGL((k_adj_b3d<K, rows, false>), dim3((unsigned)wg), dim3(64 * waves), 0, s, a);
+}
+
+__global__ void __launch_bounds__(256) k_scale_rc(int64_t n, const double* __restrict__ x, const double* __restrict__ rC,
+                                                  double* __restrict__ y) {
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
+        y[i] = x[i] * rC[i];
+}
+
+}  // namespace
+
+bool use_adj_b3d(const DevGrid& g, int face) { return face == 0 && b3d_applies(g); }
+
+void launch_psi_from_lambda(hipStream_t s, int64_t n, const double* lam, const double* rC, double* psi) {
+    const int64_t b = (n + 255) / 256;
+    hipLaunchKernelGGL(k_scale_rc, dim3((unsigned)(b < 8192 ? b : 8192)), dim3(256), 0, s, n, lam, rC, psi);
+}
+
+void launch_adj_b3d(hipStream_t s, const DevGrid& g, int K, const double* psi, const double* const v[2],
+                    const double* Lam, const double* rC, double* psi_out, double* dgpsi, double* gLam,
+                    const double cm[2], const double tb[2], double tau, int accumulate) {
+    A3Args a{};
+    a.psi = psi;
+    a.Lam = Lam;
+    a.rC = rC;
+    a.psi_out = psi_out;
+    a.dgpsi = dgpsi;
+    a.gLam = gLam;
+    for (int k = 0; k < K; ++k) {
+        a.v[k] = v[k];
+        a.cm[k] = cm[k];
+        a.tb[k] = tb[k];
+    }
+    a.nx = g.nx;
+    a.ny = g.ny;
+    a.nz = g.nz;
+    a.perx = g.per[0];
+    a.pery = g.per[1];
+    a.perz = g.per[2];
+    a.hx = 0.5 * tau * g.w[0];
+    a.hy = 0.5 * tau * g.w[1];
+    a.hz = 0.5 * tau * g.w[2];
+    if (K == 2) launch_adj_b3d_k<2>(s, g, a, accumulate != 0);
+    else launch_adj_b3d_k<1>(s, g, a, accumulate != 0);
+}
 
 }  // namespace tlim

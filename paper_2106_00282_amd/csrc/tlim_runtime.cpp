@@ -466,7 +466,7 @@ void run_lim_pass(tlim_ctx* c, const DevGrid& g, int face, double tau, const Pas
             const int k = tlim::sweeps_per_launch(g, nst - 2, true);
             if (k > 1)
                 tlim::launch_b3d<float>(s, g, face, nullptr, c->q32, c->Lam32, c->rC32, c->wb[0], ps.at(1), k, tau,
-                                        nullptr, tlim::PassSlots{}, nullptr, 0, sp(0));
+                                        nullptr, tlim::PassSlots{}, sp(0));
             else
                 tlim::launch_z3d_two_from_zero32(s, g, face, c->q32, c->Lam32, c->rC32, c->wb[0], sp(0), sp(1), tau);
             cur = c->wb[0];
@@ -2018,8 +2018,16 @@ void adj_forward_step(tlim_ctx* c, const tlim_step_opts* o, const double* lamv, 
                 bool last = m + k == nst;
                 double* nxt = last ? Tout : c->vb[pp];
                 tlim::Stages stg{nullptr, tbv.data() + m, nullptr};
-                m += tlim::launch_sweeps64(s, g, o->face_mean, cur, T0, Lam, c->rC, nxt, stg, k, last, o->dt, nullptr,
-                                           tlim::PassSlots{});
+                // (3D: by the kernel that keeps the stages, so that a step
+                // gives the same bits whether or not they are kept)
+                int done = -1;
+                if (tlim::use_z3d(g) && k > 1)
+                    done = tlim::launch_sweeps64_keep(s, g, o->face_mean, cur, T0, Lam, c->rC, nxt, stg, k, o->dt,
+                                                      nullptr, 0);
+                if (done < 0)
+                    done = tlim::launch_sweeps64(s, g, o->face_mean, cur, T0, Lam, c->rC, nxt, stg, k, last, o->dt,
+                                                 nullptr, tlim::PassSlots{});
+                m += done;
                 cur = nxt;
                 pp ^= 1;
             }
@@ -2195,20 +2203,25 @@ tlim_status tlim_adjoint_parabolic(tlim_ctx* c, const tlim_step_opts* o, int32_t
                     m -= done;
                 }
             }
-            if (!psi_form && tlim::use_adj_z3d(g, o->face_mean)) {
-                // 3D grids: reverse stages by z-marching waves in psi form
-                tlim::launch_fill(s, dg, 0.0, N);
-                tlim::launch_fill(s, gLam, 0.0, N);
+            if (!psi_form && tlim::use_adj_b3d(g, o->face_mean)) {
+                // 3D grids: reverse stages in psi form, two per launch
                 tlim::launch_psi_from_lambda(s, N, cur, c->rC, bufs[pp]);
                 cur = bufs[pp];
                 pp ^= 1;
-                for (int m = nst; m >= 1; --m) {
-                    const double tb = o->dt * b[m - 1];
-                    const double* vprev = m == 1 ? T0 : st0 + (size_t)(m - 1) * sf;
-                    tlim::launch_adj_z3d(s, g, cur, vprev, Lam, c->rC, bufs[pp], dg, gLam, 1.0 / (1.0 + tb), tb,
-                                         o->dt);
+                for (int m = nst; m >= 1;) {
+                    const int k = std::min(m, 2);
+                    const double* v[2] = {nullptr, nullptr};
+                    double cm[2] = {0.0, 0.0}, tbm[2] = {0.0, 0.0};
+                    for (int q = 0; q < k; ++q) {
+                        v[q] = m - q == 1 ? T0 : st0 + (size_t)(m - q - 1) * sf;
+                        tbm[q] = o->dt * b[m - q - 1];
+                        cm[q] = 1.0 / (1.0 + tbm[q]);
+                    }
+                    tlim::launch_adj_b3d(s, g, k, cur, v, Lam, c->rC, bufs[pp], dg, gLam, cm, tbm, o->dt,
+                                         m == nst ? 0 : 1);
                     cur = bufs[pp];
                     pp ^= 1;
+                    m -= k;
                 }
                 psi_form = true;
             }

@@ -79,25 +79,30 @@ template <typename R>
 void launch_z3d(hipStream_t s, const DevGrid& g, int face, const R* v, const R* G, const R* Lam, const R* rC, R* out,
                 StageParam sp, double tau, const double* Tit, PassSlots ps);
 // K = 2 .. 3 (double) or 4 (float) stages on a 3D grid in one launch
-// (tlim_block3d.hip), as b3d_stages gives them.  v == NULL: the input is the stage before the first from
-// w = 0, c_in G (sp_in: that stage's parameter).  With Tit != NULL (FP64, the
-// last stage the final one) also the pass reductions.  With stages != NULL
-// the result of stage s < K goes to stages + s*sstride as well.
+// (tlim_block3d.hip), as b3d_stages gives them.  v == NULL (float): the input
+// is the stage before the first from w = 0, c_in G (sp_in: that stage's
+// parameter).  With Tit != NULL (FP64, the last stage the final one) also the
+// pass reductions.  keep (FP64): with stages != NULL the result of stage s < K
+// goes to stages + s*sstride as well; with NULL the same arithmetic, bit for
+// bit, without.
 template <typename R>
 void launch_b3d(hipStream_t s, const DevGrid& g, int face, const R* v, const R* G, const R* Lam, const R* rC, R* out,
-                Stages st, int K, double tau, const double* Tit, PassSlots ps, R* stages = nullptr,
-                int64_t sstride = 0, StageParam sp_in = StageParam{nullptr, 0.0, 0.0});
+                Stages st, int K, double tau, const double* Tit, PassSlots ps,
+                StageParam sp_in = StageParam{nullptr, 0.0, 0.0}, bool keep = false, R* stages = nullptr,
+                int64_t sstride = 0);
 // Stages of the next 3D launch when `count` remain (1 where blocking does not apply).
 int b3d_stages(const DevGrid& g, int count, bool f32);
-// Reverse stages of the adjoint on 3D grids by z-marching waves (arithmetic
-// face means): psi_out = c_m (tb psi - tau rC A' psi) with the face gradient
-// and dL/dg accumulated in place into gLam and dgpsi (psi = C^-1 lambda;
-// launch_psi_from_lambda converts the first stage's input).
-bool use_adj_z3d(const DevGrid& g, int face);
+// K = 1 or 2 reverse stages of the adjoint on a 3D grid in one launch
+// (arithmetic face means): psi_out = the K stages' c_m (tb psi - tau rC A' psi)
+// from psi, the face gradient and dL/dg accumulated in place into gLam and
+// dgpsi (accumulate = 0: from zero); v[k], cm[k], tb[k] belong to the k-th
+// stage reversed (psi = C^-1 lambda; launch_psi_from_lambda converts the
+// first stage's input).
+bool use_adj_b3d(const DevGrid& g, int face);
 void launch_psi_from_lambda(hipStream_t s, int64_t n, const double* lam, const double* rC, double* psi);
-void launch_adj_z3d(hipStream_t s, const DevGrid& g, const double* psi, const double* vprev, const double* Lam,
-                    const double* rC, double* psi_out, double* dgpsi, double* gLam, double cm, double tb,
-                    double tau);
+void launch_adj_b3d(hipStream_t s, const DevGrid& g, int K, const double* psi, const double* const v[2],
+                    const double* Lam, const double* rC, double* psi_out, double* dgpsi, double* gLam,
+                    const double cm[2], const double tb[2], double tau, int accumulate);
 // The first two float stages of an FP32 pass that starts from w = 0 on a 3D
 // grid in one launch: stage 0 gives c_0 qn exactly, so the launch runs stage
 // 1 on that input read from qn (sp0, sp1: the two stages' parameters).
@@ -110,8 +115,9 @@ void launch_z3d_final32(hipStream_t s, const DevGrid& g, int face, const float* 
 
 // Blocked FP64 stages that also keep their intermediate results: the result
 // of the launch's stage k (k = 1 .. K-1) goes to stages + k*sstride and the
-// last one to out.  Returns K, or -1 where blocking does not apply (then
-// nothing is launched).
+// last one to out (3D grids: stages == NULL keeps none, with the same bits in
+// out).  Returns K, or -1 where blocking does not apply (then nothing is
+// launched).
 int launch_sweeps64_keep(hipStream_t s, const DevGrid& g, int face, const double* v, const double* rhs,
                          const double* Lam, const double* rC, double* out, Stages st, int count, double tau,
                          double* stages, int64_t sstride);

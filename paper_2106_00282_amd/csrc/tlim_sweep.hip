@@ -895,7 +895,8 @@ int launch_sweeps64_keep(hipStream_t s, const DevGrid& g, int face, const double
                                    sstride);
     const int k = b3d_stages(g, count, false);
     if (k > 1) {
-        launch_b3d<double>(s, g, face, v, rhs, Lam, rC, out, st, k, tau, nullptr, PassSlots{}, stages, sstride);
+        launch_b3d<double>(s, g, face, v, rhs, Lam, rC, out, st, k, tau, nullptr, PassSlots{},
+                           StageParam{nullptr, 0.0, 0.0}, true, stages, sstride);
         return k;
     }
     return -1;
