@@ -600,9 +600,11 @@ tlim_status viscous(tlim_ctx* c, const tlim_step_opts* o, tlim_step_report* rep,
     DevGrid g0 = dev_grid(c, kUnit);
     tlim::launch_visc_coeffs(c->stream, g0, ph, c->field[TLIM_ALPHA2], c->field[TLIM_M1], c->field[TLIM_M2], c->Lam,
                              c->rC, c->Lam32, c->rC32);
+    // 1/C and Lambda now hold the viscous coefficients (and with heating T
+    // changes before the relaxation): what the last step built is void
+    c->next_ready = false;
     const bool heat = o->visc_heating != 0;
     double* E = c->fset[TLIM_E] ? c->field[TLIM_E] : nullptr;
-    if (heat) c->next_ready = false;  // T changes before the relaxation
     if (heat && c->t2_alias) {
         // the phases are heated differently: T2 gets its own array again
         tlim::launch_copy(c->stream, c->field[TLIM_T2], c->field[TLIM_T1], c->N);
@@ -811,7 +813,10 @@ double* free_alpha2(const tlim_ctx* c) {
 bool next_step_ok(const tlim_ctx* c, const tlim_step_opts* o, const DevGrid& g) {
     // FP32 contexts: the relaxation in the launch that also runs the double
     // final stage costs about what the separate relaxation kernel does
-    return c->precision == TLIM_FP64 && next_coef_ok(c, g) && !o->cycle_mode && o->picard_tol <= 0.0;
+    // (a step with a viscous part is taken to be followed by another, which
+    // overwrites 1/C first)
+    return c->precision == TLIM_FP64 && next_coef_ok(c, g) && !o->cycle_mode && o->picard_tol <= 0.0 &&
+           !o->do_viscous;
 }
 
 tlim::NextCoef next_step_coef(tlim_ctx* c, const tlim_step_opts* o, const DevPhases& ph) {

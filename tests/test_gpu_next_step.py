@@ -1,0 +1,39 @@
+"""A step's last launch may build the next step's first coefficients.  They
+must not be taken up when the next step's viscous part has overwritten 1/C.  FP64 against the
+oracle at the bar of the 200x steps, 1e-12; P of every pass equal."""
+import numpy as np
+import pytest
+
+from paper_2106_00282_amd import workloads as W
+from paper_2106_00282_amd.tlim import StepOpts
+from _cases import make_solver, oracle_dt, rel_err
+
+pytestmark = pytest.mark.gpu
+
+
+def _steps(n, viscous, faces, npow):
+    from oracle import oracle as orc
+    wl = W.levelset2d(n)
+    wl["phases"] = W.base_phases(k0=(1.0, 0.05), npow=npow, mu=(1e-2, 1e-3))
+    if viscous:
+        rng = np.random.Generator(np.random.PCG64(n))
+        for c in "uv":
+            wl["fields"][c] = np.ascontiguousarray(0.1 * rng.standard_normal(wl["fields"]["T1"].shape))
+    tau, _ = oracle_dt(orc, wl)
+    g = orc.make_grid(wl["n"], wl["h"], wl["bc"])
+    fo = {k: v.copy() for k, v in wl["fields"].items()}
+    s = make_solver(wl)
+    for k, face in enumerate(faces):
+        st, ro = orc.step(g, wl["phases"], orc.StepOpts(tau=tau, passes=2, do_viscous=int(viscous), face_mean=face), fo)
+        st, rg = s.advance(StepOpts(dt=tau, passes=2, do_viscous=int(viscous), face_mean=face))
+        assert st == 0
+        errs = {q: rel_err(s.get_field(q).cpu().numpy(), fo[q]) for q in fo if q != "T2"}
+        print(f"case {n} viscous={viscous} step {k} face {face} P={rg['P']} oracle {ro['P']} {errs}", flush=True)
+        assert rg["P"] == ro["P"], (k, rg["lambda_G"], ro["lambda_G"])
+        assert max(errs.values()) <= 1e-12, (k, errs)
+    s.close()
+
+
+@pytest.mark.parametrize("n", [96, 256, 640])
+def test_viscous_steps(n):
+    _steps(n, True, (0, 0, 0, 0), 2.0)
