@@ -64,6 +64,7 @@ struct tlim_ctx {
     // row (zero it before any other use).
     bool next_ready, spare_clean, row0_moved;
     double next_eps;
+    int next_face;  // its bound's face mean
     double* chat_tab;            // whole-step kernel: b/lambda per P (order chat_order, -1: not built)
     int chat_order;
     unsigned* bar;               // whole-step kernel: barrier counter
@@ -842,6 +843,7 @@ tlim::NextCoef next_step_coef(tlim_ctx* c, const tlim_step_opts* o, const DevPha
 void note_next_step(tlim_ctx* c, const tlim_step_opts* o, bool done) {
     c->next_ready = done;
     c->next_eps = o->alpha_eps;
+    c->next_face = o->face_mean;
 }
 
 // pass0_done: the coefficients and bound of the first pass were built with
@@ -1541,7 +1543,8 @@ bool relax_step(tlim_ctx* c, const tlim_step_opts* o) {
     DevPhases ph = dev_phases(c);
     const bool B1 = c->phase[0].pinf != c->phase[1].pinf;
     bool pass0_done = false;
-    if (c->next_ready && c->row0_moved && fast_coeffs(c, g) && !B1 && o->alpha_eps == c->next_eps) {
+    if (c->next_ready && c->row0_moved && fast_coeffs(c, g) && !B1 && o->alpha_eps == c->next_eps &&
+        o->face_mean == c->next_face) {
         // the previous step's last launch relaxed this state already: adopt
         // its relaxed T, alpha2 and Lambda (1/C is unchanged); its bound is in the first
         // pass's row, the other pass rows are zero up to clean_rows

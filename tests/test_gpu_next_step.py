@@ -1,5 +1,6 @@
 """A step's last launch may build the next step's first coefficients.  They
-must not be taken up when the next step's viscous part has overwritten 1/C.  FP64 against the
+must not be taken up when the next step's viscous part has overwritten 1/C, or
+when it uses the other face mean (whose bound differs).  FP64 against the
 oracle at the bar of the 200x steps, 1e-12; P of every pass equal."""
 import numpy as np
 import pytest
@@ -37,3 +38,8 @@ def _steps(n, viscous, faces, npow):
 @pytest.mark.parametrize("n", [96, 256, 640])
 def test_viscous_steps(n):
     _steps(n, True, (0, 0, 0, 0), 2.0)
+
+
+@pytest.mark.parametrize("n", [96, 256, 640])
+def test_face_mean_changes(n):
+    _steps(n, False, (0, 1, 0, 1, 1, 0), 2.0)
