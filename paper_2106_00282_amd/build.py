@@ -11,7 +11,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libtlim.so")
 ARCH = "gfx950"
 
-SOURCES = ["tlim_kernels.hip", "tlim_coeffs.hip", "tlim_sweep.hip", "tlim_sweep3d.hip", "tlim_block3d.hip", "tlim_step2d.hip", "tlim_adjoint.hip", "tlim_hyperbolic.hip",
+SOURCES = ["tlim_kernels.hip", "tlim_coeffs.hip", "tlim_sweep.hip", "tlim_sweep3d.hip", "tlim_block3d.hip", "tlim_line.hip", "tlim_step2d.hip", "tlim_adjoint.hip", "tlim_hyperbolic.hip",
            "tlim_noalloc.hip",
            "tlim_runtime.cpp"]
 

@@ -475,8 +475,7 @@ void run_lim_pass(tlim_ctx* c, const DevGrid& g, int face, double tau, const Pas
             sc.launches++;
         }
         while (m < upto) {
-            // 3D grids: the final stage (in double) has a launch of its own
-            int k = tlim::sweeps_per_launch(g, g3 && m < nst - 1 ? nst - 1 - m : upto - m, true);
+            int k = tlim::sweeps_per_launch(g, tlim::final32_apart(g) && m < nst - 1 ? nst - 1 - m : upto - m, true);
             bool last = !vh && m + k == nst;
             float* nxt = cur == c->wb[0] ? c->wb[1] : c->wb[0];
             int done = tlim::launch_sweeps32(s, g, face, cur, c->q32, c->Lam32, c->rC32, nxt, ps.at(m), k, last, tau,

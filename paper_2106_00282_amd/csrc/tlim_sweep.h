@@ -78,6 +78,17 @@ bool use_z3d(const DevGrid& g);
 template <typename R>
 void launch_z3d(hipStream_t s, const DevGrid& g, int face, const R* v, const R* G, const R* Lam, const R* rC, R* out,
                 StageParam sp, double tau, const double* Tit, PassSlots ps);
+// K stages on a 1D grid in one launch (tlim_line.hip), K <= line_stages: with
+// Tit != NULL (FP64, the last stage the final one) also the pass reductions.
+bool use_line(const DevGrid& g);
+int line_stages(int count);  // stages of the next launch when `count` remain
+template <typename R>
+void launch_line(hipStream_t s, const DevGrid& g, int face, const R* v, const R* G, const R* Lam, const R* rC, R* out,
+                 Stages st, int K, double tau, const double* Tit, PassSlots ps);
+// The FP32 form's final stage has a launch of its own (1D and 3D grids, where
+// the launches before it take float stages only).
+bool final32_apart(const DevGrid& g);
+
 // K = 2 .. 3 (double) or 4 (float) stages on a 3D grid in one launch
 // (tlim_block3d.hip), as b3d_stages gives them.  v == NULL (float): the input
 // is the stage before the first from w = 0, c_in G (sp_in: that stage's

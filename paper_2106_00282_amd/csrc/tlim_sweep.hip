@@ -902,7 +902,10 @@ int launch_sweeps64_keep(hipStream_t s, const DevGrid& g, int face, const double
     return -1;
 }
 
+bool final32_apart(const DevGrid& g) { return use_z3d(g) || use_line(g); }
+
 int sweeps_per_launch(const DevGrid& g, int count, bool f32) {
+    if (use_line(g)) return line_stages(count);
     if (!use_tb2d(g, count)) return b3d_stages(g, count, f32);
     // equal launches (a launch of K stages recomputes a ring of width K, so
     // even launches waste least), as many as cost least
@@ -935,6 +938,11 @@ int launch_sweeps64(hipStream_t s, const DevGrid& g, int face, const double* v, 
         if (nc_done) *nc_done = with_nc;
         return launch_tb2d<double>(s, g, face, v, rhs, Lam, rC, out, st, count, tau, last ? Tit : nullptr, ps,
                                    nullptr, 0, nullptr, nullptr, nullptr, with_nc ? nc : nullptr);
+    }
+    if (use_line(g)) {
+        const int k = line_stages(count);
+        launch_line<double>(s, g, face, v, rhs, Lam, rC, out, st, k, tau, last ? Tit : nullptr, ps);
+        return k;
     }
     if (const int k = b3d_stages(g, count, false); k > 1) {
         launch_b3d<double>(s, g, face, v, rhs, Lam, rC, out, st, k, tau, last ? Tit : nullptr, ps);
@@ -971,6 +979,10 @@ int launch_sweeps32(hipStream_t s, const DevGrid& g, int face, const float* w, c
     if (last) {
         if (use_z3d(g)) launch_z3d_final32(s, g, face, w, rhs, Lam32, rC, out64, tau, Tit, ps);
         else launch_final32(s, g, face, w, rhs, Lam32, rC, out64, tau, Tit, ps);
+    } else if (use_line(g)) {
+        const int k = line_stages(count);
+        launch_line<float>(s, g, face, w, qn, Lam32, rC32, out, st, k, tau, nullptr, PassSlots{});
+        return k;
     } else if (const int k = b3d_stages(g, count, true); k > 1) {
         launch_b3d<float>(s, g, face, w, qn, Lam32, rC32, out, st, k, tau, nullptr, PassSlots{});
         return k;
