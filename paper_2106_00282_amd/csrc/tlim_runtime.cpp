@@ -115,6 +115,13 @@ struct tlim_ctx {
     // Consecutive verified steps whose passes all ran the P of the step
     // before's last pass (a schedule settled enough to pipeline).
     int hist_steady;
+    // How far the last verified step's bounds may move without another P
+    // (record_schedule): 0 not known, 1 and 2 enough for schedule_holds.
+    int hist_room;
+    bool hist_missed;  // the last prediction missed, and no step has held since
+    // A field of the heat step was set after the last verified step; whether
+    // the schedule held over the last such change.
+    bool state_set, set_holds;
     // After a step T_2 = T_1 everywhere: the T2 field then reads through T1.
     bool t2_alias;
     int64_t predict_misses;
@@ -743,11 +750,38 @@ struct HeatOutcome {
 // Its later passes follow the same pass of this step, extrapolated with the
 // change since the step before when that change is small (the bound drifts
 // as T smooths; a jump, e.g. from new material constants, is not a trend).
+//
+// A state set from outside starts over: nothing is extrapolated across it, and
+// whether the old schedule survived it decides if the next such change is
+// predicted at all (set_holds).  Programs that set a fresh initial state per
+// run lose a whole step's work to that miss (1024^2, ten steps a run: the
+// first step's 275 us of two pipelined steps, of 2000 us), while those
+// that exchange the state every step keep their predictions.
+//
+// hist_room: when the last two passes' bounds differ by at most 1%, the state
+// has lost its initial jumps, and the next step's bounds follow within a few
+// per cent (4% on the smooth 2D level-set states, 6% on bubbles in 3D, whose
+// passes differ by 1.8%): 1 if no P changes over 3%, 2 over 5%.
 void record_schedule(tlim_ctx* c, int passes, const double* lam, double dt) {
     bool steady = c->hist_passes == passes;
     for (int i = 0; i < passes && steady; ++i) steady = lim_P(dt, lam[i]) == c->hist_P[i];
     c->hist_steady = steady ? c->hist_steady + 1 : 0;
-    const bool have_prev = c->hist_nlam >= 1 && c->hist_passes == passes;
+    if (steady || c->state_set) c->hist_missed = false;
+    const bool have_prev = c->hist_nlam >= 1 && c->hist_passes == passes && !c->state_set;
+    if (c->state_set && c->hist_passes == passes) c->set_holds = steady;
+    c->state_set = false;
+    c->hist_room = 0;
+    if (passes > 1 && std::fabs(lam[passes - 1] - lam[passes - 2]) <= 0.01 * lam[passes - 1]) {
+        auto same = [&](double room) {
+            bool eq = true;
+            for (int i = 0; i < passes; ++i) {
+                const double l = i == 0 ? lam[passes - 1] : lam[i];
+                eq = eq && lim_P(dt, (1.0 - room) * l) == lim_P(dt, (1.0 + room) * l);
+            }
+            return eq;
+        };
+        c->hist_room = same(0.05) ? 2 : same(0.03) ? 1 : 0;
+    }
     for (int i = 0; i < passes; ++i) {
         double l = i == 0 ? lam[passes - 1] : lam[i];
         if (i > 0 && have_prev) {
@@ -759,6 +793,14 @@ void record_schedule(tlim_ctx* c, int passes, const double* lam, double dt) {
     for (int i = 0; i < passes; ++i) c->hist_lam[i] = lam[i];
     c->hist_nlam = 1;
     c->hist_passes = passes;
+}
+
+// Whether the next step's P can be predicted: the schedule has held for
+// `steps` steps, or (1: predict one step, 2: pipeline, where the prediction is
+// two steps old and a miss costs two) its bounds leave that much room.
+bool schedule_holds(const tlim_ctx* c, int passes, int steps) {
+    if (c->hist_passes != passes || (c->state_set && !c->set_holds)) return false;
+    return c->hist_steady >= steps || (!c->state_set && !c->hist_missed && c->hist_room >= steps);
 }
 
 // The blocked FP64 sweep can build the next pass's coefficients in its last
@@ -970,6 +1012,7 @@ tlim_status heat_passes(tlim_ctx* c, const tlim_step_opts* o, Mode mode, tlim_st
         record_schedule(c, out.passes_run, lv, o->dt);
     } else {
         c->hist_steady = 0;
+        c->hist_room = 0;
     }
     return TLIM_OK;
 }
@@ -1202,6 +1245,10 @@ tlim_status tlim_bind_workspace(tlim_ctx* c, void* dev_ptr, size_t bytes) {
     c->t2_alias = false;
     c->hist_passes = 0;
     c->hist_steady = 0;
+    c->hist_room = 0;
+    c->hist_missed = false;
+    c->state_set = false;
+    c->set_holds = true;
     c->hist_nlam = 0;
     c->clean_rows = c->clean_keep = 0;  // the new accumulator is not known to be zero
     zero_rows(c, tlim::kTgtFlag, tlim::kTgtNextStep + 1);
@@ -1253,6 +1300,7 @@ tlim_status tlim_set_field(tlim_ctx* c, int32_t f, const void* src, int32_t dtyp
     else
         tlim::launch_widen(c->stream, c->field[f], (const float*)src, c->N);
     c->fset[f] = true;
+    if (f == TLIM_T1 || f == TLIM_T2 || f == TLIM_ALPHA2 || f == TLIM_M1 || f == TLIM_M2) c->state_set = true;
     return TLIM_OK;
 }
 
@@ -1407,10 +1455,9 @@ namespace {
 // history to predict P from), the grid's tiles can all be resident and the
 // schedule is not given by the caller.
 bool step2d_ok(const tlim_ctx* c, const tlim_step_opts* o) {
-    // AUTO: the steps that would otherwise read each pass's bound back (no
-    // schedule history, or one that has not yet held for a step)
+    // AUTO: the steps that would otherwise read each pass's bound back
     if (o->whole_step == TLIM_WHOLE_NEVER ||
-        (o->whole_step == TLIM_WHOLE_AUTO && c->hist_passes == o->passes && c->hist_steady >= 1))
+        (o->whole_step == TLIM_WHOLE_AUTO && schedule_holds(c, o->passes, 1)))
         return false;
     if (c->precision != TLIM_FP64 || o->cycle_mode || o->frozen_lambda || o->picard_tol > 0.0) return false;
     if (c->phase[0].pinf != c->phase[1].pinf) return false;
@@ -1621,11 +1668,11 @@ tlim_status advance_sync(tlim_ctx* c, const tlim_step_opts* o, tlim_step_report*
         const bool pass0_done = relax_step(c, o);
         Mode mode = Mode::Sync;
         if (o->frozen_lambda) mode = Mode::Frozen;
-        // Predict only once the schedule has held for a step: a miss costs
-        // the whole heat part twice, a readback per pass only a round trip
-        // (where the first pass's bound keeps differing from the last pass's
-        // of the step before, every prediction would miss)
-        else if (!o->cycle_mode && o->picard_tol <= 0.0 && c->hist_passes == o->passes && c->hist_steady >= 1)
+        // Predict only once the schedule has held for a step or its bounds
+        // leave room: a miss costs the whole heat part twice, a readback per
+        // pass only a round trip (where the first pass's bound keeps differing
+        // from the last pass's of the step before, every prediction would miss)
+        else if (!o->cycle_mode && o->picard_tol <= 0.0 && schedule_holds(c, o->passes, 1))
             mode = Mode::Predict;
         st = heat_passes(c, o, mode, rep, tm, sc, out, pass0_done);
         if (st) return st;
@@ -1635,6 +1682,7 @@ tlim_status advance_sync(tlim_ctx* c, const tlim_step_opts* o, tlim_step_report*
             // roll back to the relaxed state and rerun with one readback per
             // pass; only the rerun's sweeps count
             c->predict_misses++;
+            c->hist_missed = true;
             if (B1) tlim::launch_copy(s, c->field[TLIM_ALPHA2], c->a2n, c->N);
             out = HeatOutcome{};
             sc = SweepCount{};
@@ -1685,12 +1733,12 @@ void next_result_block(tlim_ctx* c) {
 // relaxed alpha2 and T^n go to fresh arrays).
 // A pipelined step is predicted from the step two back, and a miss costs the
 // newer step too, so pipelining waits until two consecutive steps kept the
-// same schedule.
+// same schedule (or the bounds leave room for two).
 bool pipeline_ok(const tlim_ctx* c, const tlim_step_opts* o, const tlim_step_report* rep) {
     return !rep && !o->do_viscous && !o->time_sweeps && !o->cycle_mode && !o->frozen_lambda && o->picard_tol <= 0.0 &&
            !c->fset[TLIM_E] &&
            c->phase[0].pinf == c->phase[1].pinf && fast_coeffs(c, dev_grid(c, kUnit)) &&
-           c->hist_passes == o->passes && c->hist_steady >= 2 && c->res_host_dev != nullptr;
+           schedule_holds(c, o->passes, 2) && c->res_host_dev != nullptr;
 }
 
 // Enqueue a predicted step without waiting for anything: relaxation with the
@@ -1840,6 +1888,7 @@ tlim_status redo_pending(tlim_ctx* c, const tlim_ctx::Pending& p) {
     for (double* a : c->a2pool)  // a2x: the third alpha2 array
         if (a != c->field[TLIM_ALPHA2] && a != c->a2n) c->a2x = a;
     c->predict_misses++;
+    c->hist_missed = true;
     c->pipeline_redos++;
     Timer tm{c, false};
     SweepCount sc;
