@@ -173,18 +173,27 @@ __global__ void __launch_bounds__(64 * kWaves) k_coeffs2d(Coef2DArgs a) {
     }
 }
 
-// 3D grids: the same per-cell work, with each wave marching through a chunk
-// of z planes (kRows3 rows per wave) and keeping the conductivities (and g)
-// of the previous, current and next plane in registers.
+// 3D grids: the same per-cell work.  A workgroup of four waves owns 62 columns
+// by 4 kRows3 rows and marches through a chunk of z planes, each wave keeping the
+// conductivities (and g) of its kRows3 rows in the previous, current and next
+// plane in registers.  Rows next to another wave's come through LDS (one
+// barrier a plane, two buffers); the rows beyond the workgroup's are built by
+// its first and last wave.
+//
+// What bounds it: memory, at 512^3 (FP32 form, 5.4 GB a pass: 4.1 TB/s); on
+// smaller grids latency.  With independent waves the law and the relaxation ran
+// on 4 rows to write 2, and that arithmetic was the bound: 1743 us against 1322
+// at 512^3, 327 against 220 at 256^3, 37 against 29 at 128^3; with the
+// relaxation 3242 against 2636, 448 against 364 and 57 against 46.  Four rows a
+// wave need half again the registers and are slower (1450 us at 512^3).
 constexpr int kRows3 = 2;
 
 template <bool kRelax, bool kSH>
 __global__ void __launch_bounds__(64 * kWaves) k_coeffs3d(Coef2DArgs a) {
-    constexpr int RW = kRows3 + 2;
-    const int lane = threadIdx.x & 63;
-    // launch order: with the relaxation this kernel measured 8% slower in XCD order
-    const int wid = blockIdx.x * kWaves + (threadIdx.x >> 6);
-    if (wid >= a.strips) return;  // wave-uniform
+    constexpr int kRO = kRows3;
+    __shared__ double sL[2][kWaves][2][64], sg[2][kWaves][2][64];  // [plane parity][wave][first, last row]
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int wid = blockIdx.x;  // launch order: XCD order measured up to 20% slower
     const int tx = wid % a.tiles_x, rest = wid / a.tiles_x;
     const int ty = rest % a.tiles_y, tz = rest / a.tiles_y;
     const int nx = a.nx, ny = a.ny, nz = a.nz;
@@ -193,66 +202,83 @@ __global__ void __launch_bounds__(64 * kWaves) k_coeffs3d(Coef2DArgs a) {
     const bool out_lane = lane >= 1 && lane <= kOut && xg < nx;
     const bool fL = a.perx ? nx > 1 : xg > 0;
     const bool fR = a.perx ? nx > 1 : xg < nx - 1;
-    const int y0 = ty * kRows3, z0 = tz * a.zc;
+    const int y0 = (ty * kWaves + w) * kRO, z0 = tz * a.zc;
     const int z1 = z0 + a.zc < nz ? z0 + a.zc : nz;
     const bool q = a.q32 != nullptr;
+    const bool halo = w == 0 || w == kWaves - 1;  // this wave builds the row before or after its own as well
 
-    // 32-bit element offsets (the launcher requires N < 2^32)
-    unsigned rowoff[RW];
+    // 32-bit element offsets (the launcher requires N < 2^32); row kRO: the halo row
+    unsigned rowoff[kRO + 1];
 #pragma unroll
-    for (int r = 0; r < RW; ++r) rowoff[r] = (unsigned)fold(y0 - 1 + r, ny, a.pery) * (unsigned)nx + (unsigned)xi;
+    for (int r = 0; r < kRO; ++r) rowoff[r] = (unsigned)fold(y0 + r, ny, a.pery) * (unsigned)nx;
+    rowoff[kRO] = (unsigned)fold(w == 0 ? y0 - 1 : y0 + kRO, ny, a.pery) * (unsigned)nx;
     const unsigned plane = (unsigned)nx * (unsigned)ny;
-    // T, alpha2 (relaxed when kRelax), Lambda and g of the window rows of plane z
-    auto load_plane = [&](int z, double* tw, double* aw, double* Lw, double* gw) {
+    // T, alpha2 (relaxed when kRelax), 1/C, Lambda and g of the rows of plane z
+    auto load_plane = [&](int z, double* tw, double* aw, double* rw, double* Lw, double* gw, bool h) {
         const unsigned pz = (unsigned)fold(z, nz, a.perz) * plane;
         // all rows' words in flight before the first law evaluation
-        double t2w[RW], m1w[RW], m2w[RW];
+        double t2w[kRO + 1], m1w[kRO + 1], m2w[kRO + 1];
 #pragma unroll
-        for (int r = 0; r < RW; ++r) {
-            const unsigned idx = pz + rowoff[r];
+        for (int r = 0; r <= kRO; ++r) {
+            if (r == kRO && !h) continue;
+            const unsigned idx = pz + rowoff[r] + (unsigned)xi;
             tw[r] = a.T[idx];
             aw[r] = a.alpha2[idx];
             if constexpr (kRelax) t2w[r] = a.T2[idx];
             else gw[r] = q ? a.g[idx] : 0.0;
-            if constexpr (kRelax || kSH) {
+            if (kRelax || kSH || (r < kRO && a.rebuild)) {
                 m1w[r] = a.m1[idx];
                 m2w[r] = a.m2[idx];
             }
+            if (!kRelax && r < kRO && !a.rebuild) rw[r] = a.rC_in[idx];
         }
 #pragma unroll
-        for (int r = 0; r < RW; ++r) {
+        for (int r = 0; r <= kRO; ++r) {
+            if (r == kRO && !h) continue;
             if constexpr (kRelax) {
                 phys::relax_cell(a.ph, a.eps, aw[r], tw[r], t2w[r], m1w[r], m2w[r], tw[r], aw[r]);
                 gw[r] = tw[r];
             }
             if constexpr (kSH) Lw[r] = phys::cell_conductivity(a.ph, tw[r], aw[r], m1w[r] + m2w[r]);
             else Lw[r] = phys::cell_conductivity_pow(a.ph, tw[r], aw[r]);
+            if (r < kRO && (kRelax || a.rebuild)) rw[r] = inv_heat_capacity(a.ph, a.eps, tw[r], aw[r], m1w[r], m2w[r]);
         }
     };
-    // window: Lambda and g of planes z-1, z, z+1; T and alpha2 of z and z+1
-    double Lm[RW], gm[RW], tc[RW], ac[RW], Lc[RW], gc[RW], tp[RW], ap[RW], Lp[RW], gp[RW];
-    load_plane(z0 - 1, tp, ap, Lm, gm);
-    load_plane(z0, tc, ac, Lc, gc);
+    auto share = [&](int b, const double* Lw, const double* gw) {
+        sL[b][w][0][lane] = Lw[0];
+        sL[b][w][1][lane] = Lw[kRO - 1];
+        if (q) {
+            sg[b][w][0][lane] = gw[0];
+            sg[b][w][1][lane] = gw[kRO - 1];
+        }
+    };
+    // window: Lambda and g of planes z-1, z, z+1; T, alpha2 and 1/C of z and z+1
+    double Lm[kRO + 1], gm[kRO + 1], tc[kRO + 1], ac[kRO + 1], rc[kRO + 1], Lc[kRO + 1], gc[kRO + 1];
+    double tp[kRO + 1], ap[kRO + 1], rp[kRO + 1], Lp[kRO + 1], gp[kRO + 1];
+    load_plane(z0 - 1, tp, ap, rp, Lm, gm, false);
+    load_plane(z0, tc, ac, rc, Lc, gc, halo);
+    share(0, Lc, gc);
+    __syncthreads();
     double bound = 0.0;
+    int b = 0;
     for (int z = z0; z < z1; ++z) {
-        load_plane(z + 1, tp, ap, Lp, gp);
+        load_plane(z + 1, tp, ap, rp, Lp, gp, halo);
         const bool fB = a.perz ? nz > 1 : z > 0;
         const bool fF = a.perz ? nz > 1 : z < nz - 1;
-        // the output rows' m1, m2 (1/C rebuilt) or 1/C, both rows at once
-        double m1o[kRows3 + 1], m2o[kRows3 + 1], rco[kRows3 + 1];
-#pragma unroll
-        for (int r = 1; r <= kRows3; ++r) {
-            const int y = y0 + r - 1;
-            const unsigned o = out_lane && y < ny ? (unsigned)z * plane + (unsigned)y * (unsigned)nx + (unsigned)xg : 0u;
-            m1o[r] = a.rebuild ? a.m1[o] : 0.0;
-            m2o[r] = a.rebuild ? a.m2[o] : 0.0;
-            rco[r] = a.rebuild ? 0.0 : a.rC_in[o];
+        // the rows before and after this wave's own
+        const double Ldn = w == 0 ? Lc[kRO] : sL[b][w - (w > 0)][1][lane];
+        const double Lup = w == kWaves - 1 ? Lc[kRO] : sL[b][w + (w < kWaves - 1)][0][lane];
+        double gdn = 0.0, gup = 0.0;
+        if (q) {
+            gdn = w == 0 ? gc[kRO] : sg[b][w - (w > 0)][1][lane];
+            gup = w == kWaves - 1 ? gc[kRO] : sg[b][w + (w < kWaves - 1)][0][lane];
         }
 #pragma unroll
-        for (int r = 1; r <= kRows3; ++r) {
-            const int y = y0 + r - 1;
+        for (int r = 0; r < kRO; ++r) {
+            const int y = y0 + r;
             const double L = Lc[r];
             const double Ll = from_left(L), Lr = from_right(L);
+            const double Ld = r > 0 ? Lc[r > 0 ? r - 1 : 0] : Ldn, Lu = r < kRO - 1 ? Lc[r + 1] : Lup;
             const float Lf = (float)L;
             const float Llf = from_left(Lf), Lrf = from_right(Lf);
             const double gl = from_left(gc[r]), gr = from_right(gc[r]);
@@ -264,13 +290,9 @@ __global__ void __launch_bounds__(64 * kWaves) k_coeffs3d(Coef2DArgs a) {
                     a.Tn_out[o] = tc[r];
                     a.a2_out[o] = ac[r];
                 }
-                double rc;
-                if (a.rebuild) {
-                    rc = inv_heat_capacity(a.ph, a.eps, tc[r], ac[r], m1o[r], m2o[r]);
-                    a.rC[o] = rc;
-                    if (a.rC32) a.rC32[o] = (float)rc;
-                } else {
-                    rc = rco[r];
+                if (kRelax || a.rebuild) {
+                    a.rC[o] = rc[r];
+                    if (a.rC32) a.rC32[o] = (float)rc[r];
                 }
                 if (a.Lam) a.Lam[o] = L;
                 if (a.Lam32) a.Lam32[o] = Lf;
@@ -278,18 +300,19 @@ __global__ void __launch_bounds__(64 * kWaves) k_coeffs3d(Coef2DArgs a) {
                 double d = 0.0;
                 if (fL) d += a.wx * fmean<double>(L, Ll, a.face);
                 if (fR) d += a.wx * fmean<double>(L, Lr, a.face);
-                if (fD) d += a.wy * fmean<double>(L, Lc[r - 1], a.face);
-                if (fU) d += a.wy * fmean<double>(L, Lc[r + 1], a.face);
+                if (fD) d += a.wy * fmean<double>(L, Ld, a.face);
+                if (fU) d += a.wy * fmean<double>(L, Lu, a.face);
                 if (fB) d += a.wz * fmean<double>(L, Lm[r], a.face);
                 if (fF) d += a.wz * fmean<double>(L, Lp[r], a.face);
-                bound = fmax(bound, 2.0 * d * rc);
+                bound = fmax(bound, 2.0 * d * rc[r]);
                 if (q) {
-                    const double La = (double)Lf, rf = (double)(float)rc, ga = gc[r];
+                    const double La = (double)Lf, rf = (double)(float)rc[r], ga = gc[r];
+                    const double gd = r > 0 ? gc[r > 0 ? r - 1 : 0] : gdn, gu = r < kRO - 1 ? gc[r + 1] : gup;
                     double S = 0.0;
                     if (fL) S += a.wx * fmean<double>(La, (double)Llf, a.face) * (ga - gl);
                     if (fR) S += a.wx * fmean<double>(La, (double)Lrf, a.face) * (ga - gr);
-                    if (fD) S += a.wy * fmean<double>(La, (double)(float)Lc[r - 1], a.face) * (ga - gc[r - 1]);
-                    if (fU) S += a.wy * fmean<double>(La, (double)(float)Lc[r + 1], a.face) * (ga - gc[r + 1]);
+                    if (fD) S += a.wy * fmean<double>(La, (double)(float)Ld, a.face) * (ga - gd);
+                    if (fU) S += a.wy * fmean<double>(La, (double)(float)Lu, a.face) * (ga - gu);
                     if (fB) S += a.wz * fmean<double>(La, (double)(float)Lm[r], a.face) * (ga - gm[r]);
                     if (fF) S += a.wz * fmean<double>(La, (double)(float)Lp[r], a.face) * (ga - gp[r]);
                     a.q32[o] = (float)(-a.tau * rf * S);
@@ -297,12 +320,17 @@ __global__ void __launch_bounds__(64 * kWaves) k_coeffs3d(Coef2DArgs a) {
                 }
             }
         }
+        // the other buffer was last read before the last barrier
+        b ^= 1;
+        share(b, Lp, gp);
+        __syncthreads();
 #pragma unroll
-        for (int r = 0; r < RW; ++r) {
+        for (int r = 0; r <= kRO; ++r) {
             Lm[r] = Lc[r];
             gm[r] = gc[r];
             tc[r] = tp[r];
             ac[r] = ap[r];
+            rc[r] = rp[r];
             Lc[r] = Lp[r];
             gc[r] = gp[r];
         }
@@ -310,7 +338,7 @@ __global__ void __launch_bounds__(64 * kWaves) k_coeffs3d(Coef2DArgs a) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) bound = fmax(bound, __shfl_xor(bound, o, 64));
     if (lane == 0) {
-        const int sl = wid % kSlots;
+        const int sl = (wid * kWaves + w) % kSlots;
         atomicMax((unsigned long long*)(a.lam + sl), (unsigned long long)__double_as_longlong(bound + 0.0));
     }
 }
@@ -368,20 +396,23 @@ void launch_coeffs2d(hipStream_t s, const DevGrid& g, const DevPhases& ph, doubl
     a.nz = g.nz;
     a.perz = g.per[2];
     a.wz = g.w[2];
-    a.tiles_y = (g.ny + kRows3 - 1) / kRows3;
-    // z chunks sized for about 4096 waves, 4..64 planes each
+    a.tiles_y = (g.ny + kWaves * kRows3 - 1) / (kWaves * kRows3);
+    // z chunks sized for about 4096 waves, at least 4 planes each and at most
+    // 16: the workgroups in flight then work on neighbouring planes.  With the
+    // relaxation's ten streams 8 are better (512^3: 2636 us against 2755 with 16
+    // and 3560 with 64; without it 1382, 1322 and 1350).
     const int64_t cols = (int64_t)a.tiles_x * a.tiles_y;
-    int64_t zc = (int64_t)g.nz * cols / 4096;
-    zc = zc < 4 ? 4 : (zc > 64 ? 64 : zc);
+    const int64_t cap = T2_relax ? 8 : 16;
+    int64_t zc = (int64_t)g.nz * cols * kWaves / 4096;
+    zc = zc < 4 ? 4 : (zc > cap ? cap : zc);
     a.zc = (int)zc;
-    a.strips = (int)(cols * ((g.nz + a.zc - 1) / a.zc));
-    const int blocks = (a.strips + kWaves - 1) / kWaves;
+    const unsigned blocks = (unsigned)(cols * ((g.nz + a.zc - 1) / a.zc));
     if (ph.spitzer) {
-        if (T2_relax) hipLaunchKernelGGL((k_coeffs3d<true, true>), dim3((unsigned)blocks), dim3(64 * kWaves), 0, s, a);
-        else hipLaunchKernelGGL((k_coeffs3d<false, true>), dim3((unsigned)blocks), dim3(64 * kWaves), 0, s, a);
+        if (T2_relax) hipLaunchKernelGGL((k_coeffs3d<true, true>), dim3(blocks), dim3(64 * kWaves), 0, s, a);
+        else hipLaunchKernelGGL((k_coeffs3d<false, true>), dim3(blocks), dim3(64 * kWaves), 0, s, a);
     } else {
-        if (T2_relax) hipLaunchKernelGGL((k_coeffs3d<true, false>), dim3((unsigned)blocks), dim3(64 * kWaves), 0, s, a);
-        else hipLaunchKernelGGL((k_coeffs3d<false, false>), dim3((unsigned)blocks), dim3(64 * kWaves), 0, s, a);
+        if (T2_relax) hipLaunchKernelGGL((k_coeffs3d<true, false>), dim3(blocks), dim3(64 * kWaves), 0, s, a);
+        else hipLaunchKernelGGL((k_coeffs3d<false, false>), dim3(blocks), dim3(64 * kWaves), 0, s, a);
     }
 }
 
