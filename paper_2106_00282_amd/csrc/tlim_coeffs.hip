@@ -343,6 +343,230 @@ __global__ void __launch_bounds__(64 * kWaves) k_coeffs3d(Coef2DArgs a) {
     }
 }
 
+// The viscous part's coefficients and sources: a wave owns 62 columns by
+// kRowsV rows and marches a chunk of z planes with the neighbours in registers
+// (loads of the rows beside its own hit the caches), any grid.
+constexpr int kRowsV = 4;
+
+struct StripArgs {
+    // coefficients: mu = (1 - alpha2) mu_1 + alpha2 mu_2, 1/rho, bounds
+    const double* alpha2;
+    const double* m1;
+    const double* m2;
+    double* Lam;
+    double* rC;
+    float* Lam32;
+    float* rC32;
+    double* rows;  // the components' accumulator rows
+    double mu0, mu1, wc[3][3];
+    int mask;
+    // correction source
+    const double* g;
+    const double* v0;
+    const float* L32;
+    const float* r32;
+    float* q;
+    float* w0;
+    double tau, w[3];
+    int nx, ny, nz, perx, pery, perz, face, tiles_x, tiles_y, zc, strips;
+};
+
+struct Strip {
+    int xg, y0, z0, z1;
+    bool out_lane, fL, fR;
+    int64_t plane, rowoff[kRowsV + 2];
+    __device__ __forceinline__ Strip(const StripArgs& a, int wid, int lane) {
+        const int tx = wid % a.tiles_x, rest = wid / a.tiles_x;
+        const int ty = rest % a.tiles_y, tz = rest / a.tiles_y;
+        xg = tx * kOut - 1 + lane;
+        out_lane = lane >= 1 && lane <= kOut && xg < a.nx;
+        fL = a.perx ? a.nx > 1 : xg > 0;
+        fR = a.perx ? a.nx > 1 : xg < a.nx - 1;
+        y0 = ty * kRowsV;
+        z0 = tz * a.zc;
+        z1 = z0 + a.zc < a.nz ? z0 + a.zc : a.nz;
+        const int xi = fold(xg, a.nx, a.perx);
+        plane = (int64_t)a.nx * a.ny;
+#pragma unroll
+        for (int r = 0; r < kRowsV + 2; ++r) rowoff[r] = (int64_t)fold(y0 - 1 + r, a.ny, a.pery) * a.nx + xi;
+    }
+    __device__ __forceinline__ int64_t base(const StripArgs& a, int z) const { return fold(z, a.nz, a.perz) * plane; }
+};
+
+// mu, 1/rho and the Gershgorin bounds 2 rC sum_f w_f mean(mu_a, mu_b) of the
+// three velocity components.  Bound by memory: 3 arrays read, 4 written, each
+// once.  As two kernels, the second reading mu and 1/rho back per face without
+// reuse, the bounds took 219 us more at 256^3.
+__global__ void __launch_bounds__(64 * kWaves) k_visc_coeffs(StripArgs a) {
+    const int lane = threadIdx.x & 63, wid = blockIdx.x * kWaves + (threadIdx.x >> 6);
+    if (wid >= a.strips) return;  // wave-uniform
+    const Strip t(a, wid, lane);
+    auto load = [&](int z, double* L) {
+        const double* p = a.alpha2 + t.base(a, z);
+#pragma unroll
+        for (int r = 0; r < kRowsV + 2; ++r) L[r] = p[t.rowoff[r]];
+#pragma unroll
+        for (int r = 0; r < kRowsV + 2; ++r) L[r] = (1.0 - L[r]) * a.mu0 + L[r] * a.mu1;
+    };
+    double Lm[kRowsV + 2], Lc[kRowsV + 2], Lp[kRowsV + 2], mx[3] = {0.0, 0.0, 0.0};
+    load(t.z0, Lc);
+#pragma unroll
+    for (int r = 0; r < kRowsV + 2; ++r) Lm[r] = Lp[r] = 0.0;
+    if (a.nz > 1) load(t.z0 - 1, Lm);
+    for (int z = t.z0; z < t.z1; ++z) {
+        double rho[kRowsV];
+        {
+            const int64_t b = t.base(a, z);
+            double x1[kRowsV], x2[kRowsV];
+#pragma unroll
+            for (int r = 0; r < kRowsV; ++r) {
+                x1[r] = a.m1[b + t.rowoff[r + 1]];
+                x2[r] = a.m2[b + t.rowoff[r + 1]];
+            }
+            if (a.nz > 1) load(z + 1, Lp);
+#pragma unroll
+            for (int r = 0; r < kRowsV; ++r) rho[r] = x1[r] + x2[r];
+        }
+        const bool fB = a.perz ? a.nz > 1 : z > 0;
+        const bool fF = a.perz ? a.nz > 1 : z < a.nz - 1;
+#pragma unroll
+        for (int r = 1; r <= kRowsV; ++r) {
+            const int y = t.y0 + r - 1;
+            const double L = Lc[r];
+            const double Ll = from_left(L), Lr = from_right(L);
+            if (t.out_lane && y < a.ny) {
+                const int64_t o = z * t.plane + t.rowoff[r];
+                const double rc = 1.0 / rho[r - 1];
+                a.Lam[o] = L;
+                a.rC[o] = rc;
+                if (a.Lam32) {
+                    a.Lam32[o] = (float)L;
+                    a.rC32[o] = (float)rc;
+                }
+                const bool fD = a.pery ? a.ny > 1 : y > 0;
+                const bool fU = a.pery ? a.ny > 1 : y < a.ny - 1;
+                // faces in the order -x, +x, -y, +y, -z, +z
+                const double m[6] = {t.fL ? fmean<double>(L, Ll, a.face) : 0.0,
+                                     t.fR ? fmean<double>(L, Lr, a.face) : 0.0,
+                                     fD ? fmean<double>(L, Lc[r - 1], a.face) : 0.0,
+                                     fU ? fmean<double>(L, Lc[r + 1], a.face) : 0.0,
+                                     fB ? fmean<double>(L, Lm[r], a.face) : 0.0,
+                                     fF ? fmean<double>(L, Lp[r], a.face) : 0.0};
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    double d = 0.0;
+#pragma unroll
+                    for (int f = 0; f < 6; ++f) d += a.wc[c][f >> 1] * m[f];
+                    mx[c] = fmax(mx[c], 2.0 * d * rc);
+                }
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < kRowsV + 2; ++r) {
+            Lm[r] = Lc[r];
+            Lc[r] = Lp[r];
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        if (!((a.mask >> c) & 1)) continue;  // uniform
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) mx[c] = fmax(mx[c], __shfl_xor(mx[c], o, 64));
+        if (lane == 0)
+            atomicMax((unsigned long long*)(a.rows + (size_t)c * kSlots + wid % kSlots),
+                      (unsigned long long)__double_as_longlong(mx[c] + 0.0));
+    }
+}
+
+// q = -tau rC' D' g of a pass whose coefficients are already in place, from the
+// float-rounded Lambda' and rC'; w0 = v0 - g where it is not zero.  Bound by
+// memory: 3 arrays read, 1 written (20 B a cell).  One thread per cell with
+// its neighbours from memory took 213 us at 256^3.
+__global__ void __launch_bounds__(64 * kWaves) k_q32(StripArgs a) {
+    const int lane = threadIdx.x & 63, wid = blockIdx.x * kWaves + (threadIdx.x >> 6);
+    if (wid >= a.strips) return;  // wave-uniform
+    const Strip t(a, wid, lane);
+    auto load = [&](int z, double* g, float* L) {
+        const int64_t b = t.base(a, z);
+#pragma unroll
+        for (int r = 0; r < kRowsV + 2; ++r) {
+            g[r] = a.g[b + t.rowoff[r]];
+            L[r] = a.L32[b + t.rowoff[r]];
+        }
+    };
+    double gm[kRowsV + 2], gc[kRowsV + 2], gp[kRowsV + 2];
+    float Lm[kRowsV + 2], Lc[kRowsV + 2], Lp[kRowsV + 2];
+    load(t.z0, gc, Lc);
+#pragma unroll
+    for (int r = 0; r < kRowsV + 2; ++r) {
+        gm[r] = gp[r] = 0.0;
+        Lm[r] = Lp[r] = 0.0f;
+    }
+    if (a.nz > 1) load(t.z0 - 1, gm, Lm);
+    for (int z = t.z0; z < t.z1; ++z) {
+        float rc[kRowsV];
+        double v0[kRowsV];
+        {
+            const int64_t b = t.base(a, z);
+#pragma unroll
+            for (int r = 0; r < kRowsV; ++r) {
+                rc[r] = a.r32[b + t.rowoff[r + 1]];
+                v0[r] = a.w0 ? a.v0[b + t.rowoff[r + 1]] : 0.0;
+            }
+            if (a.nz > 1) load(z + 1, gp, Lp);
+        }
+        const bool fB = a.perz ? a.nz > 1 : z > 0;
+        const bool fF = a.perz ? a.nz > 1 : z < a.nz - 1;
+#pragma unroll
+        for (int r = 1; r <= kRowsV; ++r) {
+            const int y = t.y0 + r - 1;
+            const double ga = gc[r], La = (double)Lc[r];
+            const double gl = from_left(ga), gr = from_right(ga);
+            const float Ll = from_left(Lc[r]), Lr = from_right(Lc[r]);
+            if (t.out_lane && y < a.ny) {
+                const int64_t o = z * t.plane + t.rowoff[r];
+                const bool fD = a.pery ? a.ny > 1 : y > 0;
+                const bool fU = a.pery ? a.ny > 1 : y < a.ny - 1;
+                double S = 0.0;
+                if (t.fL) S += a.w[0] * fmean<double>(La, (double)Ll, a.face) * (ga - gl);
+                if (t.fR) S += a.w[0] * fmean<double>(La, (double)Lr, a.face) * (ga - gr);
+                if (fD) S += a.w[1] * fmean<double>(La, (double)Lc[r - 1], a.face) * (ga - gc[r - 1]);
+                if (fU) S += a.w[1] * fmean<double>(La, (double)Lc[r + 1], a.face) * (ga - gc[r + 1]);
+                if (fB) S += a.w[2] * fmean<double>(La, (double)Lm[r], a.face) * (ga - gm[r]);
+                if (fF) S += a.w[2] * fmean<double>(La, (double)Lp[r], a.face) * (ga - gp[r]);
+                a.q[o] = (float)(-a.tau * (double)rc[r - 1] * S);
+                if (a.w0) a.w0[o] = (float)(v0[r - 1] - ga);
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < kRowsV + 2; ++r) {
+            gm[r] = gc[r];
+            gc[r] = gp[r];
+            Lm[r] = Lc[r];
+            Lc[r] = Lp[r];
+        }
+    }
+}
+
+// Grid of a strip kernel: z chunks for about 8192 waves, 4 to 16 planes each.
+dim3 strip_grid(const DevGrid& g, int face, StripArgs& a) {
+    a.nx = g.nx;
+    a.ny = g.ny;
+    a.nz = g.nz;
+    a.perx = g.per[0];
+    a.pery = g.per[1];
+    a.perz = g.per[2];
+    a.face = face;
+    a.tiles_x = (g.nx + kOut - 1) / kOut;
+    a.tiles_y = (g.ny + kRowsV - 1) / kRowsV;
+    const int64_t cols = (int64_t)a.tiles_x * a.tiles_y;
+    int64_t zc = (int64_t)g.nz * cols / 8192;
+    zc = zc < 4 ? 4 : (zc > 16 ? 16 : zc);
+    a.zc = (int)zc;
+    a.strips = (int)(cols * ((g.nz + a.zc - 1) / a.zc));
+    return dim3((unsigned)((a.strips + kWaves - 1) / kWaves));
+}
+
 }  // namespace
 
 bool coeffs2d_applies(const DevGrid& g) { return g.nz == 1 || g.N < ((int64_t)1 << 32); }
@@ -414,6 +638,42 @@ void launch_coeffs2d(hipStream_t s, const DevGrid& g, const DevPhases& ph, doubl
         if (T2_relax) hipLaunchKernelGGL((k_coeffs3d<true, false>), dim3(blocks), dim3(64 * kWaves), 0, s, a);
         else hipLaunchKernelGGL((k_coeffs3d<false, false>), dim3(blocks), dim3(64 * kWaves), 0, s, a);
     }
+}
+
+void launch_visc_coeffs(hipStream_t s, const DevGrid& g, const DevPhases& ph, int face, const double* alpha2,
+                        const double* m1, const double* m2, double* Lam, double* rC, float* Lam32, float* rC32,
+                        const double wc[3][3], int mask, double* rows) {
+    StripArgs a{};
+    a.alpha2 = alpha2;
+    a.m1 = m1;
+    a.m2 = m2;
+    a.Lam = Lam;
+    a.rC = rC;
+    a.Lam32 = Lam32;
+    a.rC32 = rC32;
+    a.rows = rows;
+    a.mu0 = ph.mu[0];
+    a.mu1 = ph.mu[1];
+    for (int c = 0; c < 3; ++c)
+        for (int d = 0; d < 3; ++d) a.wc[c][d] = wc[c][d];
+    a.mask = mask;
+    const dim3 grid = strip_grid(g, face, a);
+    hipLaunchKernelGGL(k_visc_coeffs, grid, dim3(64 * kWaves), 0, s, a);
+}
+
+void launch_q32(hipStream_t s, const DevGrid& g, int face, const double* rhs, const double* v0,
+                const float* Lam32, const float* rC32, double tau, float* q, float* w0) {
+    StripArgs a{};
+    a.g = rhs;
+    a.v0 = v0;
+    a.L32 = Lam32;
+    a.r32 = rC32;
+    a.q = q;
+    a.w0 = w0;
+    a.tau = tau;
+    for (int d = 0; d < 3; ++d) a.w[d] = g.w[d];
+    const dim3 grid = strip_grid(g, face, a);
+    hipLaunchKernelGGL(k_q32, grid, dim3(64 * kWaves), 0, s, a);
 }
 
 }  // namespace tlim

@@ -110,10 +110,13 @@ void launch_heat_coeffs(hipStream_t s, const DevGrid& g, const DevPhases& ph, do
                         const double* Tn, const double* src1, const double* src2, double* Lam,
                         double* rC, double* rhs, float* Lam32, float* rC32);
 
-// Viscous coefficients: Lam = alpha1 mu1 + alpha2 mu2, rC = 1/(m1 + m2).
-void launch_visc_coeffs(hipStream_t s, const DevGrid& g, const DevPhases& ph, const double* alpha2,
-                        const double* m1, const double* m2, double* Lam, double* rC, float* Lam32,
-                        float* rC32);
+// Viscous coefficients Lam = alpha1 mu1 + alpha2 mu2, rC = 1/(m1 + m2), and the
+// Gershgorin bounds of the three velocity components: component c with the
+// face weights wc[c] (its axis scaled by 4/3), into rows + c*kSlots, for the
+// components with bit c of mask set.
+void launch_visc_coeffs(hipStream_t s, const DevGrid& g, const DevPhases& ph, int face, const double* alpha2,
+                        const double* m1, const double* m2, double* Lam, double* rC, float* Lam32, float* rC32,
+                        const double wc[3][3], int mask, double* rows);
 
 // Heat coefficients plus the Gershgorin bound (max into the accumulator row
 // lam) in one stencil pass over (T, alpha2).  With q32 != NULL (FP32
@@ -141,14 +144,6 @@ void launch_coeffs2d(hipStream_t s, const DevGrid& g, const DevPhases& ph, doubl
                      int rebuild, double* Lam, double* rC, float* Lam32, float* rC32, float* q32, float* w0,
                      double* lam, const double* T2_relax = nullptr, double* Tn_out = nullptr,
                      double* a2_out = nullptr);
-
-// Gershgorin bound max_i 2 rC_i sum_f w Lam_f -> max into the row lam.
-// The Gershgorin bounds of the three velocity components of the viscous part
-// in one pass over (Lambda, 1/C): component c with the face weights wc[c]
-// (its axis scaled by 4/3), into rows + c*kSlots, for the components with
-// bit c of mask set.
-void launch_gershgorin_visc(hipStream_t s, const DevGrid& g, int face, const double* Lam, const double* rC,
-                            const double wc[3][3], int mask, double* rows);
 
 // Energy sum of the state -> added to the row energy.
 void launch_energy(hipStream_t s, const DevGrid& g, const DevPhases& ph, const double* alpha2,

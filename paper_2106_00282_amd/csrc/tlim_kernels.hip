@@ -376,63 +376,7 @@ __global__ void __launch_bounds__(256) k_heat_coeffs(DevGrid g, DevPhases ph, do
     }
 }
 
-__global__ void __launch_bounds__(256) k_visc_coeffs(DevGrid g, DevPhases ph, const double* __restrict__ alpha2,
-                                                     const double* __restrict__ m1, const double* __restrict__ m2,
-                                                     double* __restrict__ Lam, double* __restrict__ rC,
-                                                     float* __restrict__ Lam32, float* __restrict__ rC32) {
-    for (int64_t a = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; a < g.N;
-         a += (int64_t)gridDim.x * blockDim.x) {
-        double a2 = alpha2[a];
-        double mu = (1.0 - a2) * ph.mu[0] + a2 * ph.mu[1];
-        double r = 1.0 / (m1[a] + m2[a]);
-        Lam[a] = mu;
-        rC[a] = r;
-        if (Lam32) {
-            Lam32[a] = (float)mu;
-            rC32[a] = (float)r;
-        }
-    }
-}
-
 // --------------------------------------------------------------- reductions
-
-// The Gershgorin bounds 2 rC sum_f w_f mean(Lambda_a, Lambda_b) of the three
-// velocity components from one read of Lambda and 1/C: per cell the face
-// means once, then each component's weighted sum (faces -x, +x, -y, +y, -z,
-// +z) and its block max.
-struct ViscW {
-    double w[3][3];
-};
-__global__ void __launch_bounds__(256) k_gershgorin_visc(DevGrid g, int face, const double* __restrict__ Lam,
-                                                         const double* __restrict__ rC, ViscW wc, int mask,
-                                                         double* rows) {
-    __shared__ double sh[16];
-    int i = blockIdx.x * TX + threadIdx.x, j = blockIdx.y * TY + threadIdx.y, k = blockIdx.z;
-    double mx[3] = {0.0, 0.0, 0.0};
-    if (i < g.nx && j < g.ny) {
-        int64_t a = i + (int64_t)g.nx * (j + (int64_t)g.ny * k);
-        Faces f;
-        faces_of(g, i, j, k, f);
-        const double La = Lam[a], rc = rC[a];
-        double m[6];
-#pragma unroll
-        for (int q = 0; q < 6; ++q) m[q] = f.has[q] ? face_mean<double>(La, Lam[a + f.off[q]], face) : 0.0;
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            double d = 0.0;
-#pragma unroll
-            for (int q = 0; q < 6; ++q)
-                if (f.has[q]) d += wc.w[c][q >> 1] * m[q];
-            mx[c] = 2.0 * d * rc;
-        }
-    }
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        if (!((mask >> c) & 1)) continue;  // uniform
-        const double b = block_max(mx[c], sh);
-        if (flat_tid() == 0) atomic_max_nonneg(rows + (size_t)c * kSlots + block_slot(), b);
-    }
-}
 
 __global__ void __launch_bounds__(256) k_energy(DevGrid g, DevPhases ph, const double* __restrict__ alpha2,
                                                 const double* __restrict__ m1, const double* __restrict__ m2,
@@ -538,20 +482,6 @@ __global__ void __launch_bounds__(256) k_final64(DevGrid g, int face, const doub
         if (Tit) acc.add(t, Tit[a]);
     }
     if (Tit) acc.store(ps);
-}
-
-__global__ void __launch_bounds__(256) k_q32(DevGrid g, int face, const double* __restrict__ rhs,
-                                             const double* __restrict__ v0, const float* __restrict__ Lam32,
-                                             const float* __restrict__ rC32, double tau, float* __restrict__ q,
-                                             float* __restrict__ w0) {
-    int i = blockIdx.x * TX + threadIdx.x, j = blockIdx.y * TY + threadIdx.y, k = blockIdx.z;
-    if (i >= g.nx || j >= g.ny) return;
-    int64_t a = i + (int64_t)g.nx * (j + (int64_t)g.ny * k);
-    Faces f;
-    faces_of(g, i, j, k, f);
-    double S = stencil<double, double, float>(g, f, a, rhs, Lam32, face);
-    q[a] = (float)(-tau * (double)rC32[a] * S);
-    if (w0) w0[a] = (float)(v0[a] - rhs[a]);  // (not needed where v0 is rhs: w0 = 0)
 }
 
 __global__ void __launch_bounds__(256) k_stage32(DevGrid g, int face, const float* __restrict__ w,
@@ -815,21 +745,6 @@ void launch_heat_coeffs_bound(hipStream_t s, const DevGrid& g, const DevPhases& 
                            rC, rhs, Lam32, rC32, q32, w0, lam);
 }
 
-void launch_visc_coeffs(hipStream_t s, const DevGrid& g, const DevPhases& ph, const double* alpha2,
-                        const double* m1, const double* m2, double* Lam, double* rC, float* Lam32, float* rC32) {
-    hipLaunchKernelGGL(k_visc_coeffs, dim3(pointwise_blocks(g.N)), dim3(kReduceThreads), 0, s, g, ph, alpha2, m1, m2,
-                       Lam, rC, Lam32, rC32);
-}
-
-void launch_gershgorin_visc(hipStream_t s, const DevGrid& g, int face, const double* Lam, const double* rC,
-                            const double wc[3][3], int mask, double* rows) {
-    ViscW w;
-    for (int c = 0; c < 3; ++c)
-        for (int d = 0; d < 3; ++d) w.w[c][d] = wc[c][d];
-    hipLaunchKernelGGL(k_gershgorin_visc, tile_grid(g), dim3(TX, TY), 0, s, g, face, Lam, rC, w, mask, rows);
-}
-
-
 void launch_energy(hipStream_t s, const DevGrid& g, const DevPhases& ph, const double* alpha2, const double* m1,
                    const double* m2, const double* T1, const double* T2, double* energy) {
     hipLaunchKernelGGL(k_energy, dim3(reduce_blocks(g.N)), dim3(kReduceThreads), 0, s, g, ph, alpha2, m1, m2, T1, T2,
@@ -844,11 +759,6 @@ void launch_stage64(hipStream_t s, const DevGrid& g, int face, const double* v, 
 void launch_final64(hipStream_t s, const DevGrid& g, int face, const double* v, const double* rhs,
                     const double* Lam, const double* rC, double* out, double tau, const double* Tit, PassSlots ps) {
     hipLaunchKernelGGL(k_final64, tile_grid(g), dim3(TX, TY), 0, s, g, face, v, rhs, Lam, rC, out, tau, Tit, ps);
-}
-
-void launch_q32(hipStream_t s, const DevGrid& g, int face, const double* rhs, const double* v0,
-                const float* Lam32, const float* rC32, double tau, float* q, float* w0) {
-    hipLaunchKernelGGL(k_q32, tile_grid(g), dim3(TX, TY), 0, s, g, face, rhs, v0, Lam32, rC32, tau, q, w0);
 }
 
 void launch_stage32(hipStream_t s, const DevGrid& g, int face, const float* w, const float* q,

@@ -493,7 +493,8 @@ void run_lim_pass(tlim_ctx* c, const DevGrid& g, int face, double tau, const Pas
             sc.launches++;
         }
         if (vh) {
-            tlim::launch_final32(s, g, face, cur, rhs, c->Lam32, c->rC, out, tau, Tit, slots);
+            if (g3) tlim::launch_z3d_final32(s, g, face, cur, rhs, c->Lam32, c->rC, out, tau, Tit, slots);
+            else tlim::launch_final32(s, g, face, cur, rhs, c->Lam32, c->rC, out, tau, Tit, slots);
             sc.launches++;
             vh->g64 = rhs;
             vh->w32 = cur;
@@ -517,7 +518,11 @@ void run_lim_pass(tlim_ctx* c, const DevGrid& g, int face, double tau, const Pas
             sc.launches++;
         }
         if (vh) {
-            tlim::launch_final64(s, g, face, cur, rhs, c->Lam, c->rC, out, tau, Tit, slots);
+            if (tlim::use_z3d(g))
+                tlim::launch_z3d<double>(s, g, face, cur, rhs, c->Lam, c->rC, out, tlim::StageParam{nullptr, 0.0, 0.0},
+                                         tau, Tit, slots);
+            else
+                tlim::launch_final64(s, g, face, cur, rhs, c->Lam, c->rC, out, tau, Tit, slots);
             sc.launches++;
             vh->v64 = cur;
         }
@@ -605,8 +610,21 @@ double cell_volume(const tlim_ctx* c) { return c->h[0] * c->h[1] * c->h[2]; }
 tlim_status viscous(tlim_ctx* c, const tlim_step_opts* o, tlim_step_report* rep, Timer& tm, SweepCount& sc) {
     DevPhases ph = dev_phases(c);
     DevGrid g0 = dev_grid(c, kUnit);
-    tlim::launch_visc_coeffs(c->stream, g0, ph, c->field[TLIM_ALPHA2], c->field[TLIM_M1], c->field[TLIM_M2], c->Lam,
-                             c->rC, c->Lam32, c->rC32);
+    // the components' bounds depend on (Lambda, 1/C) only, which the passes
+    // do not change: all of them from one kernel and one readback
+    double lam_c[3] = {0.0, 0.0, 0.0};
+    double wc[3][3];
+    int mask = 0;
+    for (int comp = 0; comp < 3; ++comp) {
+        double scale[3] = {1.0, 1.0, 1.0};
+        scale[comp] = 4.0 / 3.0;
+        const DevGrid gc = dev_grid(c, scale);
+        for (int d = 0; d < 3; ++d) wc[comp][d] = gc.w[d];
+        if (!o->frozen_visc && c->n[comp] > 1) mask |= 1 << comp;
+    }
+    if (mask) zero_rows(c, tlim::kTgtVisc, tlim::kTgtVisc + 3);
+    tlim::launch_visc_coeffs(c->stream, g0, ph, o->face_mean, c->field[TLIM_ALPHA2], c->field[TLIM_M1],
+                             c->field[TLIM_M2], c->Lam, c->rC, c->Lam32, c->rC32, wc, mask, row(c, tlim::kTgtVisc));
     // 1/C and Lambda now hold the viscous coefficients (and with heating T
     // changes before the relaxation): what the last step built is void
     c->next_ready = false;
@@ -617,21 +635,7 @@ tlim_status viscous(tlim_ctx* c, const tlim_step_opts* o, tlim_step_report* rep,
         tlim::launch_copy(c->stream, c->field[TLIM_T2], c->field[TLIM_T1], c->N);
         c->t2_alias = false;
     }
-    // the components' bounds depend on (Lambda, 1/C) only, which the passes
-    // do not change: all of them from one kernel and one readback
-    double lam_c[3] = {0.0, 0.0, 0.0};
     if (!o->frozen_visc) {
-        double wc[3][3];
-        int mask = 0;
-        for (int comp = 0; comp < 3; ++comp) {
-            double scale[3] = {1.0, 1.0, 1.0};
-            scale[comp] = 4.0 / 3.0;
-            const DevGrid gc = dev_grid(c, scale);
-            for (int d = 0; d < 3; ++d) wc[comp][d] = gc.w[d];
-            if (c->n[comp] > 1) mask |= 1 << comp;
-        }
-        zero_rows(c, tlim::kTgtVisc, tlim::kTgtVisc + 3);
-        tlim::launch_gershgorin_visc(c->stream, g0, o->face_mean, c->Lam, c->rC, wc, mask, row(c, tlim::kTgtVisc));
         tlim_status st = read_result(c, tlim::kTgtVisc, tlim::kTgtVisc + 3);
         if (st) return st;
         for (int comp = 0; comp < 3; ++comp) lam_c[comp] = result(c, tlim::kTgtVisc + comp);
