@@ -48,7 +48,9 @@ struct Coef2DArgs {
     const double* T;      // T^(it); with relaxation: T1
     const double* T2;     // with relaxation
     double* Tn_out;       // with relaxation: the relaxed T
-    double* a2_out;       // with relaxation: the relaxed alpha2
+    double* a2_out;       // with relaxation or the update: the new alpha2
+    const double* Tit;    // with the update: the iterate before T
+    const double* a2n;    // with the update: the relaxed alpha2 (alpha2 at T^n)
     const double* alpha2;
     const double* m1;
     const double* m2;
@@ -69,7 +71,13 @@ struct Coef2DArgs {
     double wz;
 };
 
-template <bool kRelax, bool kSH>
+// With kUpdate (unequal p_inf) the pass before this one ends here: alpha2 of the
+// interface cells follows the new T, d alpha2 = -B1/(T^2 W) dT from the step's start
+// with the coefficient at (T^(it), alpha2^(it)), on every row of the strip, and
+// goes to an array of its own.  As a kernel of its own (15.4 us at 1024^2, then
+// 16.0 for this one) the update reads T, T^(it), T^n, both alpha2 and m1, m2, most of
+// which the coefficients need again; together 21.6 us.
+template <bool kRelax, bool kSH, bool kUpdate = false>
 __global__ void __launch_bounds__(64 * kWaves) k_coeffs2d(Coef2DArgs a) {
     const int lane = threadIdx.x & 63;
     const int strip = tb::xcd_block() * kWaves + (threadIdx.x >> 6);  // strips in XCD order
@@ -90,16 +98,20 @@ __global__ void __launch_bounds__(64 * kWaves) k_coeffs2d(Coef2DArgs a) {
     // relaxation, the Spitzer-Harm law and 1/C, and 1/C itself when kept.
     double Lw[kRows + 2], tw[kRows + 2], aw[kRows + 2], gw[kRows + 2];
     double m1w[kRows + 2], m2w[kRows + 2], rcw[kRows + 2];
-    const bool need_m = kRelax || kSH || a.rebuild;
+    const bool need_m = kRelax || kSH || kUpdate || a.rebuild;
     {
-        double t2w[kRows + 2];
+        double t2w[kRows + 2], tiw[kRows + 2], anw[kRows + 2];
 #pragma unroll
         for (int r = 0; r < kRows + 2; ++r) {
             const int64_t idx = at(y0 - 1 + r);
             tw[r] = a.T[idx];
             aw[r] = a.alpha2[idx];
             if constexpr (kRelax) t2w[r] = a.T2[idx];
-            else gw[r] = q ? a.g[idx] : 0.0;
+            else gw[r] = kUpdate || q ? a.g[idx] : 0.0;
+            if constexpr (kUpdate) {
+                tiw[r] = a.Tit[idx];
+                anw[r] = a.a2n[idx];
+            }
             m1w[r] = need_m ? a.m1[idx] : 0.0;
             m2w[r] = need_m ? a.m2[idx] : 0.0;
             rcw[r] = a.rebuild ? 0.0 : a.rC_in[idx];
@@ -110,6 +122,13 @@ __global__ void __launch_bounds__(64 * kWaves) k_coeffs2d(Coef2DArgs a) {
                 phys::relax_cell(a.ph, a.eps, aw[r], tw[r], t2w[r], m1w[r], m2w[r], tw[r], aw[r]);
                 gw[r] = tw[r];  // g = T^n, the relaxed T
             }
+        }
+        if constexpr (kUpdate) {
+            const double B1 = a.ph.pinf[0] - a.ph.pinf[1];
+#pragma unroll
+            for (int r = 0; r < kRows + 2; ++r)
+                if (phys::is_mixed(anw[r], a.eps))
+                    aw[r] = phys::updated_alpha2(a.ph, B1, anw[r], aw[r], tw[r], tiw[r], gw[r], m1w[r], m2w[r]);
         }
     }
 #pragma unroll
@@ -131,10 +150,8 @@ __global__ void __launch_bounds__(64 * kWaves) k_coeffs2d(Coef2DArgs a) {
             const int64_t o = (int64_t)y * a.nx + xg;
             const bool fD = a.pery ? a.ny > 1 : y > 0;
             const bool fU = a.pery ? a.ny > 1 : y < a.ny - 1;
-            if constexpr (kRelax) {
-                a.Tn_out[o] = tw[r];
-                a.a2_out[o] = aw[r];
-            }
+            if constexpr (kRelax) a.Tn_out[o] = tw[r];
+            if constexpr (kRelax || kUpdate) a.a2_out[o] = aw[r];
             double rc;
             if (a.rebuild) {
                 rc = inv_heat_capacity(a.ph, a.eps, tw[r], aw[r], m1w[r], m2w[r]);
@@ -574,8 +591,11 @@ bool coeffs2d_applies(const DevGrid& g) { return g.nz == 1 || g.N < ((int64_t)1 
 void launch_coeffs2d(hipStream_t s, const DevGrid& g, const DevPhases& ph, double eps, double tau, int face,
                      const double* T, const double* alpha2, const double* m1, const double* m2, const double* Tn,
                      int rebuild, double* Lam, double* rC, float* Lam32, float* rC32, float* q32, float* w0,
-                     double* lam, const double* T2_relax, double* Tn_out, double* a2_out) {
+                     double* lam, const double* T2_relax, double* Tn_out, double* a2_out, const double* Tit,
+                     const double* a2n) {
     Coef2DArgs a{};
+    a.Tit = Tit;
+    a.a2n = a2n;
     a.ph = ph;
     a.T = T;
     a.T2 = T2_relax;
@@ -608,7 +628,10 @@ void launch_coeffs2d(hipStream_t s, const DevGrid& g, const DevPhases& ph, doubl
     if (g.nz == 1) {
         a.strips = a.tiles_x * ((g.ny + kRows - 1) / kRows);
         const int blocks = (a.strips + kWaves - 1) / kWaves;
-        if (ph.spitzer) {
+        if (Tit) {
+            if (ph.spitzer) hipLaunchKernelGGL((k_coeffs2d<false, true, true>), dim3((unsigned)blocks), dim3(64 * kWaves), 0, s, a);
+            else hipLaunchKernelGGL((k_coeffs2d<false, false, true>), dim3((unsigned)blocks), dim3(64 * kWaves), 0, s, a);
+        } else if (ph.spitzer) {
             if (T2_relax) hipLaunchKernelGGL((k_coeffs2d<true, true>), dim3((unsigned)blocks), dim3(64 * kWaves), 0, s, a);
             else hipLaunchKernelGGL((k_coeffs2d<false, true>), dim3((unsigned)blocks), dim3(64 * kWaves), 0, s, a);
         } else {

@@ -42,6 +42,14 @@ static __device__ __forceinline__ double pressure_stiffness(const DevPhases& ph,
     return (ph.gamma[0] - 1.0) * C1 / (a1 * a1) + (ph.gamma[1] - 1.0) * C2 / (a2 * a2);
 }
 
+// alpha2 of an interface cell after a pass from the step's start (Tn, a2n) to
+// tn: d alpha2 = -B1/(T^2 W) dT, coefficient lagged at (ti, a2it).
+static __device__ __forceinline__ double updated_alpha2(const DevPhases& ph, double B1, double a2n, double a2it,
+                                                        double tn, double ti, double Tn, double m1, double m2) {
+    const double W = pressure_stiffness(ph, a2it, m1 * ph.cv[0], m2 * ph.cv[1]);
+    return a2n - B1 / (ti * ti * W) * (tn - Tn);
+}
+
 // Coulomb logarithm of the Spitzer-Harm law (Sec. 4.4) from ln T and
 // ln rho: ln(l_D / max(l_LD, l_dB)), floored at 1, with ln l_D =
 // ln sh_D + (ln T - ln rho)/2, ln l_LD = ln sh_LD - ln T and

@@ -137,13 +137,14 @@ void launch_heat_coeffs_bound(hipStream_t s, const DevGrid& g, const DevPhases& 
 // T = T1, T2_relax, m1, m2) -- as launch_relax -- and builds the coefficients
 // at the relaxed state (rebuild implied); the relaxed T goes to Tn_out (also
 // g, so Tn is not read), the relaxed alpha2 to a2_out (alpha2 itself is not
-// written).
+// written).  With Tit != NULL (2D) alpha2 is first updated as by
+// launch_pass_update from (T, Tit, Tn, a2n) and goes to a2_out.
 bool coeffs2d_applies(const DevGrid& g);
 void launch_coeffs2d(hipStream_t s, const DevGrid& g, const DevPhases& ph, double eps, double tau, int face,
                      const double* T, const double* alpha2, const double* m1, const double* m2, const double* Tn,
                      int rebuild, double* Lam, double* rC, float* Lam32, float* rC32, float* q32, float* w0,
                      double* lam, const double* T2_relax = nullptr, double* Tn_out = nullptr,
-                     double* a2_out = nullptr);
+                     double* a2_out = nullptr, const double* Tit = nullptr, const double* a2n = nullptr);
 
 // Energy sum of the state -> added to the row energy.
 void launch_energy(hipStream_t s, const DevGrid& g, const DevPhases& ph, const double* alpha2,
@@ -178,6 +179,7 @@ void launch_final32(hipStream_t s, const DevGrid& g, int face, const float* w, c
                     const float* Lam32, const double* rC, double* out, double tau, const double* Tit, PassSlots ps);
 
 // After a pass: alpha2 update (B1 != 0) and the pass reductions into ps.
+// (reductions only where ps.tmax is set)
 void launch_pass_update(hipStream_t s, const DevGrid& g, const DevPhases& ph, double eps,
                         const double* Tit, const double* Tnew, const double* Tn, const double* alpha2n,
                         const double* alpha2it, const double* m1, const double* m2, double* alpha2out,

@@ -393,6 +393,8 @@ __global__ void __launch_bounds__(256) k_energy(DevGrid g, DevPhases ph, const d
     if (threadIdx.x == 0) atomicAdd(energy + block_slot(), e);
 }
 
+// End of a pass: alpha2 of the interface cells, and the pass reductions where
+// no stage took them (cycle mode: ps.tmax set).
 __global__ void __launch_bounds__(256) k_pass_update(DevGrid g, DevPhases ph, double eps,
                                                      const double* __restrict__ Tit, const double* __restrict__ Tnew,
                                                      const double* __restrict__ Tn, const double* __restrict__ alpha2n,
@@ -400,19 +402,15 @@ __global__ void __launch_bounds__(256) k_pass_update(DevGrid g, DevPhases ph, do
                                                      const double* __restrict__ m2, double* alpha2out,
                                                      PassSlots ps) {
     double B1 = ph.pinf[0] - ph.pinf[1];
+    const bool reduce = ps.tmax != nullptr;
     PassAcc acc;
     for (int64_t a = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; a < g.N;
          a += (int64_t)gridDim.x * blockDim.x) {
-        double tn = Tnew[a], ti = Tit[a];
-        acc.add(tn, ti);
-        // d alpha2 = -B1/(T^2 W) dT from the step start, coefficient lagged at (T^(it), alpha2^(it))
-        if (B1 != 0.0 && is_mixed(alpha2n[a], eps)) {
-            double C1 = m1[a] * ph.cv[0], C2 = m2[a] * ph.cv[1];
-            double W = pressure_stiffness(ph, alpha2it[a], C1, C2);
-            alpha2out[a] = alpha2n[a] - B1 / (ti * ti * W) * (tn - Tn[a]);
-        }
+        if (reduce) acc.add(Tnew[a], Tit[a]);
+        if (B1 != 0.0 && is_mixed(alpha2n[a], eps))
+            alpha2out[a] = phys::updated_alpha2(ph, B1, alpha2n[a], alpha2it[a], Tnew[a], Tit[a], Tn[a], m1[a], m2[a]);
     }
-    acc.store(ps);
+    if (reduce) acc.store(ps);
 }
 
 __global__ void __launch_bounds__(256) k_be_residual(DevGrid g, int face, const double* __restrict__ v,

@@ -665,13 +665,24 @@ tlim_status viscous(tlim_ctx* c, const tlim_step_opts* o, tlim_step_report* rep,
     return TLIM_OK;
 }
 
+// Whether the next pass's coefficient launch can end this pass (2D grids
+// without sources, unequal p_inf; the alpha2 it writes needs the third array,
+// which only pipelined steps -- equal p_inf -- use otherwise).
+bool update_with_coeffs(const tlim_ctx* c, const DevGrid& g, const tlim_step_opts* o) {
+    return g.nz == 1 && !o->cycle_mode && !(c->fset[TLIM_SRC1] || c->fset[TLIM_SRC2]) &&
+           c->phase[0].pinf != c->phase[1].pinf;
+}
+
 // Heat-conduction coefficients of pass `it` at the current iterate (T1,
 // alpha2) and the Gershgorin bound (max into *lam); sets c->g_heat.
 bool fast_coeffs(const tlim_ctx* c, const DevGrid& g) {
     return !(c->fset[TLIM_SRC1] || c->fset[TLIM_SRC2]) && tlim::coeffs2d_applies(g);
 }
 
-void heat_coeffs(tlim_ctx* c, const DevGrid& g, const DevPhases& ph, const tlim_step_opts* o, double* lam, int it) {
+// Tprev != NULL: the pass before left its alpha2 update to this launch
+// (update_with_coeffs), from the iterate Tprev it started from.
+void heat_coeffs(tlim_ctx* c, const DevGrid& g, const DevPhases& ph, const tlim_step_opts* o, double* lam, int it,
+                 const double* Tprev = nullptr) {
     // T^(0) is the relaxed state T^n
     const double* T = it == 0 ? c->Tn : c->field[TLIM_T1];
     if (fast_coeffs(c, g)) {
@@ -680,7 +691,9 @@ void heat_coeffs(tlim_ctx* c, const DevGrid& g, const DevPhases& ph, const tlim_
         const bool need_lam64 = c->precision == TLIM_FP64 || o->cycle_mode;
         tlim::launch_coeffs2d(c->stream, g, ph, o->alpha_eps, o->dt, o->face_mean, T, c->field[TLIM_ALPHA2],
                               c->field[TLIM_M1], c->field[TLIM_M2], c->Tn, rebuild ? 1 : 0,
-                              need_lam64 ? c->Lam : nullptr, c->rC, c->Lam32, c->rC32, c->q32, nullptr, lam);
+                              need_lam64 ? c->Lam : nullptr, c->rC, c->Lam32, c->rC32, c->q32, nullptr, lam, nullptr,
+                              nullptr, Tprev ? c->a2x : nullptr, Tprev, c->a2n);
+        if (Tprev) std::swap(c->field[TLIM_ALPHA2], c->a2x);
         c->g_heat = c->Tn;
         c->w0_zero = true;
         return;
@@ -907,9 +920,11 @@ tlim_status heat_passes(tlim_ctx* c, const tlim_step_opts* o, Mode mode, tlim_st
         return tmax > 0.0 ? dmax / tmax : dmax;
     };
     bool coef_ready = pass0_done;  // this pass's coefficients were built by the step before it
+    const double* Tprev = nullptr;  // set: the pass before left its alpha2 update to the coefficients
     for (it = 0; it < o->passes; ++it) {
-        if (!coef_ready) heat_coeffs(c, g, ph, o, row(c, tlim::tgt_lam(it)), it);
+        if (!coef_ready) heat_coeffs(c, g, ph, o, row(c, tlim::tgt_lam(it)), it, Tprev);
         coef_ready = false;
+        Tprev = nullptr;
         // previous iterate T^(it) (T^(0) = T^n)
         const double* Tit = it == 0 ? c->Tn : c->field[TLIM_T1];
         double lam = 0.0;
@@ -961,7 +976,7 @@ tlim_status heat_passes(tlim_ctx* c, const tlim_step_opts* o, Mode mode, tlim_st
             bool done = false;
             // timed only behind the step's earlier passes (not after a readback)
             tm.skip = mode == Mode::Sync || it == 0;
-            run_lim_pass(c, g, o->face_mean, o->dt, ps, c->Tn, c->g_heat, c->Tnew, need_update ? nullptr : Tit,
+            run_lim_pass(c, g, o->face_mean, o->dt, ps, c->Tn, c->g_heat, c->Tnew, Tit,
                          pass_slots(c, it, rep != nullptr || o->picard_tol > 0.0), tm, sc, true, nullptr,
                          want || want_step ? &nc : nullptr, &done);
             if (want_step) note_next_step(c, o, done);
@@ -970,10 +985,13 @@ tlim_status heat_passes(tlim_ctx* c, const tlim_step_opts* o, Mode mode, tlim_st
                 adopt_next_coef(c);
             }
         }
-        if (need_update) {
+        if (it + 1 < o->passes && update_with_coeffs(c, g, o)) {
+            Tprev = Tit;  // (T^n, or the array T_new swaps with below)
+        } else if (need_update) {
             tlim::launch_pass_update(s, g, ph, o->alpha_eps, Tit, c->Tnew, c->Tn, c->a2n,
                                      c->field[TLIM_ALPHA2], c->field[TLIM_M1], c->field[TLIM_M2],
-                                     c->field[TLIM_ALPHA2], pass_slots(c, it));
+                                     c->field[TLIM_ALPHA2],
+                                     o->cycle_mode ? pass_slots(c, it) : tlim::PassSlots{});
         }
         std::swap(c->field[TLIM_T1], c->Tnew);
     }
