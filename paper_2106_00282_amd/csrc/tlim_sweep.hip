@@ -241,6 +241,16 @@ __global__ void __launch_bounds__(64 * NW, 4) k_tb2d(TBArgs<R> a) {
     const int ylo = a.pery ? -(1 << 30) : 0, yhi = a.pery ? 1 << 30 : a.ny - 1;
     auto face_above = [&](int y) { return (int)(y >= ylo) & (int)(y < yhi); };
     auto yout = [&](int r) { const int row = wv * RW + r; return row >= H && row < EXT_Y - H && yg0 + r < a.ny; };
+    // Output rows and the rows next to them: the others need no conductivity of
+    // the next pass.  With Spitzer-Harm laws its evaluation is half of a
+    // launch's time (517 x 301: 13 of 24 us), so rows that need none skip it,
+    // and with them whole waves (4 of 16 at H = 9 on 64 rows, one per SIMD:
+    // 22.5 us); under the power law the tests cost what they save.
+    auto near_out = [&](int r) {
+        const int row = wv * RW + r;
+        return !kSH || (row >= H - 1 && row <= EXT_Y - H && yg0 + r <= a.ny);
+    };
+    const bool near_wave = !kSH || (wv * RW + RW >= H && wv * RW <= EXT_Y - H && yg0 <= a.ny);
 
     constexpr bool kFloat = sizeof(R) == 4;
     const bool fin = kFloat && a.g64 != nullptr;
@@ -542,7 +552,8 @@ __global__ void __launch_bounds__(64 * NW, 4) k_tb2d(TBArgs<R> a) {
 #pragma unroll
                     for (int j = 0; j < C; ++j) {
                         const double tn = Tfin[r][j];
-                        Ln[r][j] = law(tn, a2v[r][j], m1v[r][j], m2v[r][j]);
+                        if constexpr (kSH) Ln[r][j] = near_out(r) ? law(tn, a2v[r][j], m1v[r][j], m2v[r][j]) : 0.0;
+                        else Ln[r][j] = law(tn, a2v[r][j], m1v[r][j], m2v[r][j]);
                     }
                 __shared__ double esh[4][WAVES][C][64];  // seams of Lambda and g
 #pragma unroll
@@ -695,40 +706,49 @@ __global__ void __launch_bounds__(64 * NW, 4) k_tb2d(TBArgs<R> a) {
             // so under the power law they are read in interface cells only
             // (the other lanes read the row's first word).
             double Ln[RW][C], a2v[RW][C], m1v[RW][C], m2v[RW][C];
-#pragma unroll
-            for (int r = 0; r < RW; ++r) ld(a.alpha2, r, a2v[r]);
             if constexpr (kSH) {
-#pragma unroll
-                for (int r = 0; r < RW; ++r) {
-                    ld(a.m1, r, m1v[r]);
-                    ld(a.m2, r, m2v[r]);
-                }
-            } else if (next_step) {
 #pragma unroll
                 for (int r = 0; r < RW; ++r)
 #pragma unroll
-                    for (int j = 0; j < C; ++j) {
-                        const bool mx = phys::is_mixed(a2v[r][j], a.eps);
-                        const unsigned xm = mx ? sx + (sel[j] ? 0u : 1u) : 0u;
-                        m1v[r][j] = row(a.m1, r)[xm];
-                        m2v[r][j] = row(a.m2, r)[xm];
+                    for (int j = 0; j < C; ++j) Ln[r][j] = a2v[r][j] = 0.0;
+            }
+            if (near_wave) {
+#pragma unroll
+                for (int r = 0; r < RW; ++r) ld(a.alpha2, r, a2v[r]);
+                if constexpr (kSH) {
+#pragma unroll
+                    for (int r = 0; r < RW; ++r) {
+                        ld(a.m1, r, m1v[r]);
+                        ld(a.m2, r, m2v[r]);
                     }
-            }
-            if (next_step) {
+                } else if (next_step) {
 #pragma unroll
-                for (int r = 0; r < RW; ++r)
+                    for (int r = 0; r < RW; ++r)
 #pragma unroll
-                    for (int j = 0; j < C; ++j)
-                        if (phys::is_mixed(a2v[r][j], a.eps))
-                            phys::relax_equal_pinf(a.ph, v[r][j], m1v[r][j], m2v[r][j], v[r][j], a2v[r][j]);
-            }
-            if constexpr (kSH) {
+                        for (int j = 0; j < C; ++j) {
+                            const bool mx = phys::is_mixed(a2v[r][j], a.eps);
+                            const unsigned xm = mx ? sx + (sel[j] ? 0u : 1u) : 0u;
+                            m1v[r][j] = row(a.m1, r)[xm];
+                            m2v[r][j] = row(a.m2, r)[xm];
+                        }
+                }
+                if (next_step) {
 #pragma unroll
-                for (int r = 0; r < RW; ++r)
+                    for (int r = 0; r < RW; ++r)
 #pragma unroll
-                    for (int j = 0; j < C; ++j) Ln[r][j] = law(v[r][j], a2v[r][j], m1v[r][j], m2v[r][j]);
-            } else {
-                phys::lambda_rows(a.ph, v, a2v, Ln);
+                        for (int j = 0; j < C; ++j)
+                            if (phys::is_mixed(a2v[r][j], a.eps))
+                                phys::relax_equal_pinf(a.ph, v[r][j], m1v[r][j], m2v[r][j], v[r][j], a2v[r][j]);
+                }
+                if constexpr (kSH) {
+#pragma unroll
+                    for (int r = 0; r < RW; ++r)
+#pragma unroll
+                        for (int j = 0; j < C; ++j)
+                            if (near_out(r)) Ln[r][j] = law(v[r][j], a2v[r][j], m1v[r][j], m2v[r][j]);
+                } else {
+                    phys::lambda_rows(a.ph, v, a2v, Ln);
+                }
             }
             // the seam buffer not used by the last stage: its reads all
             // precede that stage's barrier
@@ -751,7 +771,7 @@ __global__ void __launch_bounds__(64 * NW, 4) k_tb2d(TBArgs<R> a) {
                 Lup[j] = wv < WAVES - 1 ? sh_lo[b2][wv < WAVES - 1 ? wv + 1 : wv][j][lane] : Ln[RW - 1][j];
             }
             double bound = 0.0;
-            {
+            if (near_wave) {
 #pragma unroll
                 for (int r = 0; r < RW; ++r)
 #pragma unroll
