@@ -64,8 +64,8 @@ enum { TLIM_ORDER_INTERLEAVED = 0, TLIM_ORDER_PAPER = 1, TLIM_ORDER_ASCENDING = 
 enum { TLIM_FACE_ARITH = 0, TLIM_FACE_HARMONIC = 1 };
 /* whole_step: AUTO uses the one-launch step for the steps whose P would
  * otherwise be read back pass by pass: while the context has no schedule
- * history for the step's pass count, or one that has not yet held for a
- * step (a step is predicted only after that), on grids large enough that
+ * history for the step's pass count, or one that has neither held for a step
+ * nor leaves its bounds room (a step is predicted only then), on grids large enough that
  * blocked launches would use tiles as large as its own; ALWAYS for every
  * eligible step, NEVER for none. */
 enum { TLIM_WHOLE_AUTO = 0, TLIM_WHOLE_ALWAYS = 1, TLIM_WHOLE_NEVER = 2 };

@@ -7,7 +7,7 @@
 // waves never exchange anything: no LDS, no barrier.
 //
 // What bounds it: a launch's latency.  The 23 stages of a 1024-cell step took
-// 23 launches of 3.5 us (one stage each); here they are one launch of 5.4 us.
+// 23 launches of 3.5 us (one stage each); here they are one launch of 6.9 us.
 //
 // The operations and their order are those of the one-stage kernels (k_stage64,
 // k_final64, k_stage32), so the bits are too: S = (w mean)_left (v_a - v_left)
