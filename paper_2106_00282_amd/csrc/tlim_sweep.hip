@@ -371,18 +371,30 @@ __global__ void __launch_bounds__(64 * NW, 4) k_tb2d(TBArgs<R> a) {
     // In double the stages run on V^(s) = Q_s v^(s), Q_s = prod_{k<s} (1 + tau b_k):
     //   V^(s+1) = Q_s G + tau b_s V^(s) - sum_f kappa_f (V_a - V_f)^(s),
     // one product per cell and stage less than with the factor c_s.  Lane s
-    // holds Q_s and 1/Q_(s+1) (10 factors of at most 1 + tau lambda).
-    double pQ = 1.0, piQ = 1.0;
+    // holds Q_s and 1/Q_(s+1).  The products are carried as pairs (hi + lo): each
+    // Q_s is then rounded once, and what Q_(s+1) / Q_s is off from 1 + tau b_s, alike in
+    // every cell and launch, does not add up over a run (products in one double
+    // left 2.5e-14 after 10 steps where the factors c_s left 4e-15).
+    double pQ = 1.0, piQ = 1.0, Qk = 1.0;
     if constexpr (!kFloat) {
-        double inc = 1.0 + ptb;  // inclusive product over the lanes up to this one
+        double hi = 1.0 + ptb;  // inclusive product over the lanes up to this one
+        const double bb = hi - 1.0;
+        double lo = (1.0 - (hi - bb)) + (ptb - bb);
 #pragma unroll
         for (int o = 1; o < 16; o <<= 1) {
-            const double up = __shfl_up(inc, o, 64);
-            if (lane >= o) inc *= up;
+            const double uh = __shfl_up(hi, o, 64), ul = __shfl_up(lo, o, 64);
+            const double p = hi * uh;
+            const double e = fma(hi, uh, -p) + fma(hi, ul, lo * uh);
+            const double q = p + e;
+            if (lane >= o) {
+                lo = e - (q - p);
+                hi = q;
+            }
         }
-        const double below = __shfl_up(inc, 1, 64);
+        const double below = __shfl_up(hi, 1, 64);
         pQ = lane == 0 ? 1.0 : below;
-        piQ = 1.0 / inc;
+        piQ = 1.0 / hi;
+        Qk = lane_value(hi, K - 1);
     }
     // Stage s exchanges the seam rows through LDS buffer (s+1)&1; buffer 0
     // held the Lambda seams, whose reads all precede the first barrier below.
@@ -465,11 +477,12 @@ __global__ void __launch_bounds__(64 * NW, 4) k_tb2d(TBArgs<R> a) {
         }
     }
     if constexpr (!kFloat) {
-        const double iq = lane_value(piQ, K - 1);
+        // (1/Q_K and what its rounding left out)
+        const double iq = lane_value(piQ, K - 1), ir = iq * fma(-Qk, iq, 1.0);
 #pragma unroll
         for (int r = 0; r < RW; ++r)
 #pragma unroll
-            for (int j = 0; j < C; ++j) v[r][j] *= iq;
+            for (int j = 0; j < C; ++j) v[r][j] = fma(v[r][j], iq, v[r][j] * ir);
     }
     // Final stage (b = 0) of the FP32 correction form, in double on v = g + w:
     // T = g - tau rC64 sum_f w_f mean(Lambda'_a, Lambda'_b) (v_a - v_b), with
