@@ -54,7 +54,10 @@ typedef enum {
     TLIM_E_HIP = 3,      /* a HIP runtime call failed */
     TLIM_E_NOMEM = 4,    /* bound workspace smaller than required */
     TLIM_E_NOCONV = 5,   /* Picard or cycle tolerance not met; fields hold the last iterate */
-    TLIM_E_NUMERIC = 6   /* non-finite or non-positive temperature found after a pass */
+    TLIM_E_NUMERIC = 6   /* non-finite or non-positive temperature found after a pass, or a
+                          * spectral bound that is not finite (or asks for more than 2^30
+                          * Chebyshev parameters): no pass can run, the fields hold the last
+                          * iterate */
 } tlim_status;
 
 enum { TLIM_PERIODIC = 0, TLIM_ADIABATIC = 1 };         /* boundary per axis */

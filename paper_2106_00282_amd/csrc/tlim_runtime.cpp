@@ -14,6 +14,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <new>
 #include <string>
 #include <vector>
 
@@ -232,8 +233,13 @@ DevPhases dev_phases(const tlim_ctx* c) { return tlim::pack_phases(c->phase); }
 
 // ---------------------------------------------------------------- schedule
 
-// Number of Chebyshev parameters of one LIM pass (Sec. 3.2).
-int lim_P(double tau, double lambda_max) { return (int)std::ceil(kPi / 4.0 * std::sqrt(tau * lambda_max + 1.0)); }
+// Number of Chebyshev parameters of one LIM pass (Sec. 3.2); 0 where there is
+// no schedule: lambda_max is not finite (a state that holds an infinite
+// temperature), or the 2P - 1 stages are more than an int counts.
+int lim_P(double tau, double lambda_max) {
+    const double P = std::ceil(kPi / 4.0 * std::sqrt(tau * lambda_max + 1.0));
+    return P >= 1.0 && P < (double)(1 << 30) ? (int)P : 0;
+}
 
 // Parameters b_1..b_{2P-1} (Sec. 3.2): a_j = lambda (beta_1 - beta_j)/(1 + beta_1)
 // with beta_j = cos((2j-1) pi/(2P)) the roots of T_P, beta_1 the largest.  The
@@ -323,8 +329,12 @@ tlim_status check_opts(tlim_ctx* c, const tlim_step_opts* o) {
     }
     if (o->frozen_lambda)
         for (int i = 0; i < o->passes; ++i)
-            if (!(o->frozen_lambda[i] >= 0.0) || !std::isfinite(o->frozen_lambda[i]))
+            if (!(o->frozen_lambda[i] >= 0.0) || lim_P(o->dt, o->frozen_lambda[i]) == 0)
                 return fail(c, TLIM_E_ARG, "frozen_lambda[%d] invalid", i);
+    if (o->do_viscous && o->frozen_visc)
+        for (int d = 0; d < 3; ++d)
+            if (c->n[d] > 1 && lim_P(o->dt, o->frozen_visc[d]) == 0)
+                return fail(c, TLIM_E_ARG, "frozen_visc[%d] invalid", d);
     return TLIM_OK;
 }
 
@@ -405,22 +415,36 @@ struct PassSchedule {
     }
 };
 
+// Both without a stage where there is no schedule (lim_P) or no host memory
+// for it: nothing is thrown across the ABI.
 PassSchedule host_schedule(double tau, double lam, int order) {
     PassSchedule ps;
-    int P = lim_P(tau, lam);
-    std::vector<double> b = lim_params(P, lam, order);
-    ps.nst = (int)b.size();
-    ps.tb.resize(b.size());
-    for (size_t m = 0; m < b.size(); ++m) ps.tb[m] = tau * b[m];
+    const int P = lim_P(tau, lam);
+    if (P == 0) return ps;
+    try {
+        std::vector<double> b = lim_params(P, lam, order);
+        ps.tb.resize(b.size());
+        for (size_t m = 0; m < b.size(); ++m) ps.tb[m] = tau * b[m];
+        ps.nst = (int)b.size();
+    } catch (const std::bad_alloc&) {
+    }
     return ps;
 }
 
 PassSchedule device_schedule(int P, int order, const double* lam_dev) {
     PassSchedule ps;
-    ps.chat = lim_params(P, 1.0, order);
-    ps.nst = (int)ps.chat.size();
     ps.lam_dev = lam_dev;
+    try {
+        ps.chat = lim_params(P, 1.0, order);
+        ps.nst = (int)ps.chat.size();
+    } catch (const std::bad_alloc&) {
+    }
     return ps;
+}
+
+tlim_status no_schedule(tlim_ctx* c, const char* what, int i, double tau, double lam) {
+    if (lim_P(tau, lam) != 0) return fail(c, TLIM_E_NOMEM, "%s %d: no host memory for the schedule", what, i);
+    return fail(c, TLIM_E_NUMERIC, "%s %d: no schedule for the spectral bound %g", what, i, lam);
 }
 
 // out = LIM pass (eqs. LIM, LIM_last) from v0 with right-hand side rhs and the
@@ -638,7 +662,11 @@ tlim_status viscous(tlim_ctx* c, const tlim_step_opts* o, tlim_step_report* rep,
     if (!o->frozen_visc) {
         tlim_status st = read_result(c, tlim::kTgtVisc, tlim::kTgtVisc + 3);
         if (st) return st;
-        for (int comp = 0; comp < 3; ++comp) lam_c[comp] = result(c, tlim::kTgtVisc + comp);
+        for (int comp = 0; comp < 3; ++comp) {
+            lam_c[comp] = result(c, tlim::kTgtVisc + comp);
+            if (c->n[comp] > 1 && lim_P(o->dt, lam_c[comp]) == 0)
+                return no_schedule(c, "velocity component", comp, o->dt, lam_c[comp]);
+        }
     }
     for (int comp = 0; comp < 3; ++comp) {
         if (c->n[comp] <= 1) continue;
@@ -647,6 +675,7 @@ tlim_status viscous(tlim_ctx* c, const tlim_step_opts* o, tlim_step_report* rep,
         DevGrid g = dev_grid(c, scale);
         const double lam = o->frozen_visc ? o->frozen_visc[comp] : lam_c[comp];
         PassSchedule ps = host_schedule(o->dt, lam, o->order);
+        if (ps.nst == 0) return no_schedule(c, "velocity component", comp, o->dt, lam);
         double* u = c->field[TLIM_U + comp];
         Vhat vh;
         tm.skip = true;  // the viscous passes are left out of the sweep timing
@@ -806,9 +835,10 @@ void record_schedule(tlim_ctx* c, int passes, const double* lam, double dt) {
             if (std::fabs(d) <= 0.1 * lam[i]) l += d;
         }
         c->hist_P[i] = lim_P(dt, l > 0.0 ? l : 0.0);
+        if (c->hist_P[i] == 0) passes = 0;  // (nothing to predict from)
     }
     for (int i = 0; i < passes; ++i) c->hist_lam[i] = lam[i];
-    c->hist_nlam = 1;
+    c->hist_nlam = passes > 0 ? 1 : 0;
     c->hist_passes = passes;
 }
 
@@ -954,6 +984,13 @@ tlim_status heat_passes(tlim_ctx* c, const tlim_step_opts* o, Mode mode, tlim_st
             P = lim_P(o->dt, lam);
             ps = host_schedule(o->dt, lam, o->order);
             if (rep) rep->lambda_G[it] = lam;
+        }
+        if (ps.nst == 0) {
+            // the step ends with the iterate it has (T^(0) = T^n)
+            if (it == 0) tlim::launch_copy(s, c->field[TLIM_T1], c->Tn, c->N);
+            if (rep) rep->passes_run = it;
+            c->hist_passes = c->hist_nlam = c->hist_steady = c->hist_room = 0;
+            return no_schedule(c, "pass", it, o->dt, lam);
         }
         P_used[it] = P;
         if (rep) rep->P[it] = P;
@@ -1547,8 +1584,9 @@ void step2d_result(const PassResult* r, int passes, Step2DResult& o) {
     for (int i = 0; i < passes; ++i) {
         o.lam[i] = r->v[tlim::tgt_lam(i)];
         const double P = r->v[tlim::kTgtP0 + i];
-        o.P[i] = (int)P;
-        if (r->v[tlim::kTgtFlag] > 0.0 && !(P >= 1.0 && P <= kStepPmax)) o.out_of_range = true;
+        const bool in_range = P >= 1.0 && P <= kStepPmax;
+        o.P[i] = in_range ? (int)P : 0;
+        if (r->v[tlim::kTgtFlag] > 0.0 && !in_range) o.out_of_range = true;
     }
     if (r->v[tlim::kTgtFlag] > 0.0 && !o.out_of_range) o.timeout = true;
 }
@@ -1780,8 +1818,8 @@ void enqueue_predicted(tlim_ctx* c, const tlim_step_opts* o, tlim_ctx::Pending& 
         if (!coef_ready) heat_coeffs(c, g, ph, o, row(c, tlim::tgt_lam(it)), it);
         const double* Tit = it == 0 ? c->Tn : c->field[TLIM_T1];
         const int P = c->hist_P[it];
-        p.P_used[it] = P;
         PassSchedule ps = device_schedule(P, o->order, row(c, tlim::tgt_lam(it)));
+        p.P_used[it] = ps.nst > 0 ? P : 0;  // (0: the check redoes the step)
         const bool last = it + 1 == o->passes;
         const bool want = !last && next_coef_ok(c, g);
         const bool want_step = last && next_step_ok(c, o, g);
@@ -2032,6 +2070,11 @@ AdjLayout adj_layout(int64_t N, int passes, int Pmax, int keep = 1) {
     off += d * (size_t)passes;
     L.step = off;
     off = L.step * (size_t)keep;
+    // (a size that no size_t holds is no size that is ever given)
+    if ((double)L.step * keep + 16.0 * (double)d > 9e18 || (double)d * passes * L.nst > 9e18) {
+        L.total = SIZE_MAX;
+        return L;
+    }
     size_t* rest[] = {&L.mu, &L.acc, &L.dg, &L.gLam, &L.lamA, &L.lamB};
     for (size_t* p : rest) {
         *p = off;
@@ -2142,7 +2185,7 @@ tlim_status tlim_adjoint_workspace_bytes(const tlim_ctx* c, const tlim_step_opts
         return TLIM_E_ARG;
     int Pmax = 1;
     for (int k = 0; k < nsteps * o->passes; ++k) {
-        if (!(lam[k] >= 0.0) || !std::isfinite(lam[k])) return TLIM_E_ARG;
+        if (!(lam[k] >= 0.0) || lim_P(o->dt, lam[k]) == 0) return TLIM_E_ARG;
         Pmax = std::max(Pmax, lim_P(o->dt, lam[k]));
     }
     *bytes = adj_layout(c->N, o->passes, Pmax).total;
@@ -2174,7 +2217,7 @@ tlim_status tlim_adjoint_parabolic(tlim_ctx* c, const tlim_step_opts* o, int32_t
     const int np = o->passes;
     int Pmax = 1;
     for (int k = 0; k < nsteps * np; ++k) {
-        if (!(lam[k] >= 0.0) || !std::isfinite(lam[k])) return fail(c, TLIM_E_ARG, "schedule entry %d invalid", k);
+        if (!(lam[k] >= 0.0) || lim_P(o->dt, lam[k]) == 0) return fail(c, TLIM_E_ARG, "schedule entry %d invalid", k);
         Pmax = std::max(Pmax, lim_P(o->dt, lam[k]));
     }
     AdjLayout L = adj_layout(c->N, np, Pmax);
