@@ -106,19 +106,22 @@ struct tlim_ctx {
     int clean_rows, clean_keep;
     hipEvent_t ev[kMaxEvents];
     hipEvent_t ev_sync;  // readback completion (polled)
-    // Schedule history for P prediction: P of each Picard pass of the last
-    // completed step (hist_passes = 0: none).
+    // Schedule history for P prediction: the bound of each Picard pass of the
+    // next step, as the last verified step predicts it (hist_passes = 0:
+    // none); the next step's dt makes P of it.
     int hist_passes;
-    int hist_P[TLIM_MAX_PASSES];
+    double hist_next[TLIM_MAX_PASSES];
     // lambda_G per pass of the last verified step (hist_nlam = 1: present)
     double hist_lam[TLIM_MAX_PASSES];
     int hist_nlam;
-    // Consecutive verified steps whose passes all ran the P of the step
-    // before's last pass (a schedule settled enough to pipeline).
+    // Consecutive verified steps whose passes all ran the P predicted from
+    // the step before (a schedule settled enough to pipeline).
     int hist_steady;
-    // How far the last verified step's bounds may move without another P
-    // (record_schedule): 0 not known, 1 and 2 enough for schedule_holds.
-    int hist_room;
+    // The last verified step's passes ended on nearly one bound, under the laws
+    // that still hold, with this face mean and threshold (record_schedule).
+    bool hist_close;
+    int hist_face;
+    double hist_eps;
     bool hist_missed;  // the last prediction missed, and no step has held since
     // A field of the heat step was set after the last verified step; whether
     // the schedule held over the last such change.
@@ -804,50 +807,54 @@ struct HeatOutcome {
 // first step's 275 us of two pipelined steps, of 2000 us), while those
 // that exchange the state every step keep their predictions.
 //
-// hist_room: when the last two passes' bounds differ by at most 1%, the state
+// hist_close: when the last two passes' bounds differ by at most 1%, the state
 // has lost its initial jumps, and the next step's bounds follow within a few
 // per cent (4% on the smooth 2D level-set states, 6% on bubbles in 3D, whose
-// passes differ by 1.8%): 1 if no P changes over 3%, 2 over 5%.
-void record_schedule(tlim_ctx* c, int passes, const double* lam, double dt) {
+// passes differ by 1.8%; other states were not measured, and a miss costs time
+// only): schedule_holds asks whether that leaves every P as it is.
+void record_schedule(tlim_ctx* c, const tlim_step_opts& o, int passes, const double* lam) {
     bool steady = c->hist_passes == passes;
-    for (int i = 0; i < passes && steady; ++i) steady = lim_P(dt, lam[i]) == c->hist_P[i];
+    for (int i = 0; i < passes && steady; ++i) steady = lim_P(o.dt, lam[i]) == lim_P(o.dt, c->hist_next[i]);
     c->hist_steady = steady ? c->hist_steady + 1 : 0;
     if (steady || c->state_set) c->hist_missed = false;
     const bool have_prev = c->hist_nlam >= 1 && c->hist_passes == passes && !c->state_set;
     if (c->state_set && c->hist_passes == passes) c->set_holds = steady;
     c->state_set = false;
-    c->hist_room = 0;
-    if (passes > 1 && std::fabs(lam[passes - 1] - lam[passes - 2]) <= 0.01 * lam[passes - 1]) {
-        auto same = [&](double room) {
-            bool eq = true;
-            for (int i = 0; i < passes; ++i) {
-                const double l = i == 0 ? lam[passes - 1] : lam[i];
-                eq = eq && lim_P(dt, (1.0 - room) * l) == lim_P(dt, (1.0 + room) * l);
-            }
-            return eq;
-        };
-        c->hist_room = same(0.05) ? 2 : same(0.03) ? 1 : 0;
-    }
+    c->hist_close = passes > 1 && std::fabs(lam[passes - 1] - lam[passes - 2]) <= 0.01 * lam[passes - 1];
+    c->hist_face = o.face_mean;
+    c->hist_eps = o.alpha_eps;
     for (int i = 0; i < passes; ++i) {
         double l = i == 0 ? lam[passes - 1] : lam[i];
         if (i > 0 && have_prev) {
             const double d = lam[i] - c->hist_lam[i];
             if (std::fabs(d) <= 0.1 * lam[i]) l += d;
         }
-        c->hist_P[i] = lim_P(dt, l > 0.0 ? l : 0.0);
-        if (c->hist_P[i] == 0) passes = 0;  // (nothing to predict from)
+        c->hist_next[i] = l > 0.0 ? l : 0.0;
     }
     for (int i = 0; i < passes; ++i) c->hist_lam[i] = lam[i];
-    c->hist_nlam = passes > 0 ? 1 : 0;
+    c->hist_nlam = 1;
     c->hist_passes = passes;
 }
 
-// Whether the next step's P can be predicted: the schedule has held for
-// `steps` steps, or (1: predict one step, 2: pipeline, where the prediction is
-// two steps old and a miss costs two) its bounds leave that much room.
-bool schedule_holds(const tlim_ctx* c, int passes, int steps) {
-    if (c->hist_passes != passes || (c->state_set && !c->set_holds)) return false;
-    return c->hist_steady >= steps || (!c->state_set && !c->hist_missed && c->hist_room >= steps);
+// Whether the P of a step with these options can be predicted: the schedule
+// has held for `steps` steps, or (1: predict one step, 2: pipeline, where the
+// prediction is two steps old and a miss costs two) its bounds may move by 3%
+// (5%) without another P at this dt.  New laws, another face mean or threshold
+// move the bounds by more than that: such a step has no room.
+bool schedule_holds(const tlim_ctx* c, const tlim_step_opts* o, int steps) {
+    if (c->hist_passes != o->passes || (c->state_set && !c->set_holds)) return false;
+    const int n = o->passes;
+    for (int i = 0; i < n; ++i)
+        if (lim_P(o->dt, c->hist_next[i]) == 0) return false;
+    if (c->hist_steady >= steps) return true;
+    if (c->state_set || c->hist_missed || !c->hist_close || o->face_mean != c->hist_face || o->alpha_eps != c->hist_eps)
+        return false;
+    const double room = steps >= 2 ? 0.05 : 0.03;
+    for (int i = 0; i < n; ++i) {
+        const double l = i == 0 ? c->hist_lam[n - 1] : c->hist_lam[i];
+        if (lim_P(o->dt, (1.0 - room) * l) != lim_P(o->dt, (1.0 + room) * l)) return false;
+    }
+    return true;
 }
 
 // The blocked FP64 sweep can build the next pass's coefficients in its last
@@ -978,7 +985,7 @@ tlim_status heat_passes(tlim_ctx* c, const tlim_step_opts* o, Mode mode, tlim_st
         PassSchedule ps;
         int P;
         if (mode == Mode::Predict) {
-            P = c->hist_P[it];
+            P = lim_P(o->dt, c->hist_next[it]);
             ps = device_schedule(P, o->order, row(c, tlim::tgt_lam(it)));
         } else {
             P = lim_P(o->dt, lam);
@@ -989,7 +996,7 @@ tlim_status heat_passes(tlim_ctx* c, const tlim_step_opts* o, Mode mode, tlim_st
             // the step ends with the iterate it has (T^(0) = T^n)
             if (it == 0) tlim::launch_copy(s, c->field[TLIM_T1], c->Tn, c->N);
             if (rep) rep->passes_run = it;
-            c->hist_passes = c->hist_nlam = c->hist_steady = c->hist_room = 0;
+            c->hist_passes = c->hist_nlam = c->hist_steady = 0;
             return no_schedule(c, "pass", it, o->dt, lam);
         }
         P_used[it] = P;
@@ -1068,10 +1075,10 @@ tlim_status heat_passes(tlim_ctx* c, const tlim_step_opts* o, Mode mode, tlim_st
         // this step's last pass.
         double lv[TLIM_MAX_PASSES];
         for (int i = 0; i < out.passes_run; ++i) lv[i] = result(c, tlim::tgt_lam(i));
-        record_schedule(c, out.passes_run, lv, o->dt);
+        record_schedule(c, *o, out.passes_run, lv);
     } else {
         c->hist_steady = 0;
-        c->hist_room = 0;
+        c->hist_close = false;
     }
     return TLIM_OK;
 }
@@ -1304,7 +1311,7 @@ tlim_status tlim_bind_workspace(tlim_ctx* c, void* dev_ptr, size_t bytes) {
     c->t2_alias = false;
     c->hist_passes = 0;
     c->hist_steady = 0;
-    c->hist_room = 0;
+    c->hist_close = false;
     c->hist_missed = false;
     c->state_set = false;
     c->set_holds = true;
@@ -1338,6 +1345,7 @@ tlim_status tlim_set_phase(tlim_ctx* c, int32_t k, const tlim_phase* p) {
     if (const char* why = tlim::check_phase(p)) return fail(c, TLIM_E_ARG, "%s", why);
     c->phase[k] = *p;
     c->phase_set[k] = true;
+    c->hist_close = false;  // other laws, other bounds
     return TLIM_OK;
 }
 
@@ -1516,7 +1524,7 @@ namespace {
 bool step2d_ok(const tlim_ctx* c, const tlim_step_opts* o) {
     // AUTO: the steps that would otherwise read each pass's bound back
     if (o->whole_step == TLIM_WHOLE_NEVER ||
-        (o->whole_step == TLIM_WHOLE_AUTO && schedule_holds(c, o->passes, 1)))
+        (o->whole_step == TLIM_WHOLE_AUTO && schedule_holds(c, o, 1)))
         return false;
     if (c->precision != TLIM_FP64 || o->cycle_mode || o->frozen_lambda || o->picard_tol > 0.0) return false;
     if (c->phase[0].pinf != c->phase[1].pinf) return false;
@@ -1633,7 +1641,7 @@ tlim_status step2d_sync(tlim_ctx* c, const tlim_step_opts* o, tlim_step_report* 
         }
     }
     sc.launches += 1;
-    record_schedule(c, o->passes, r.lam, o->dt);
+    record_schedule(c, *o, o->passes, r.lam);
     return TLIM_OK;
 }
 
@@ -1732,7 +1740,7 @@ tlim_status advance_sync(tlim_ctx* c, const tlim_step_opts* o, tlim_step_report*
         // leave room: a miss costs the whole heat part twice, a readback per
         // pass only a round trip (where the first pass's bound keeps differing
         // from the last pass's of the step before, every prediction would miss)
-        else if (!o->cycle_mode && o->picard_tol <= 0.0 && schedule_holds(c, o->passes, 1))
+        else if (!o->cycle_mode && o->picard_tol <= 0.0 && schedule_holds(c, o, 1))
             mode = Mode::Predict;
         st = heat_passes(c, o, mode, rep, tm, sc, out, pass0_done);
         if (st) return st;
@@ -1798,7 +1806,7 @@ bool pipeline_ok(const tlim_ctx* c, const tlim_step_opts* o, const tlim_step_rep
     return !rep && !o->do_viscous && !o->time_sweeps && !o->cycle_mode && !o->frozen_lambda && o->picard_tol <= 0.0 &&
            !c->fset[TLIM_E] &&
            c->phase[0].pinf == c->phase[1].pinf && fast_coeffs(c, dev_grid(c, kUnit)) &&
-           schedule_holds(c, o->passes, 2) && c->res_host_dev != nullptr;
+           schedule_holds(c, o, 2) && c->res_host_dev != nullptr;
 }
 
 // Enqueue a predicted step without waiting for anything: relaxation with the
@@ -1817,7 +1825,7 @@ void enqueue_predicted(tlim_ctx* c, const tlim_step_opts* o, tlim_ctx::Pending& 
     for (int it = 0; it < o->passes; ++it) {
         if (!coef_ready) heat_coeffs(c, g, ph, o, row(c, tlim::tgt_lam(it)), it);
         const double* Tit = it == 0 ? c->Tn : c->field[TLIM_T1];
-        const int P = c->hist_P[it];
+        const int P = lim_P(o->dt, c->hist_next[it]);
         PassSchedule ps = device_schedule(P, o->order, row(c, tlim::tgt_lam(it)));
         p.P_used[it] = ps.nst > 0 ? P : 0;  // (0: the check redoes the step)
         const bool last = it + 1 == o->passes;
@@ -1968,7 +1976,7 @@ tlim_status resolve(tlim_ctx* c) {
     Verdict v = verify(c, p);
     if (v.st) return v.st;
     if (v.mispredicted) return redo_pending(c, p);
-    record_schedule(c, p.o.passes, v.lam, p.o.dt);
+    record_schedule(c, p.o, p.o.passes, v.lam);
     if (v.bad > 0.0) return fail(c, TLIM_E_NUMERIC, "%.0f cells with non-finite or non-positive T", v.bad);
     return TLIM_OK;
 }
@@ -2017,7 +2025,7 @@ tlim_status tlim_advance_parabolic(tlim_ctx* c, const tlim_step_opts* o, tlim_st
         if (st) return st;
         return advance_sync(c, o, nullptr);
     }
-    record_schedule(c, prev.o.passes, v.lam, prev.o.dt);
+    record_schedule(c, prev.o, prev.o.passes, v.lam);
     c->pending = true;
     c->pend = np;
     if (v.bad > 0.0)
