@@ -50,6 +50,7 @@ using tb::from_left;
 using tb::from_right;
 
 constexpr int KMAX3 = 4;
+constexpr int kWaves3 = 8;  // waves per workgroup
 constexpr int kCUs = 256;
 
 template <typename R>
@@ -389,32 +390,57 @@ constexpr int b3_kmax() {
 
 // Columns of ox x oy results and the z chunks of a launch of K stages: one
 // workgroup per CU at a time, each walking its chunk and 2K planes more; the
-// count of chunks with the fewest planes walked in turn.
-int z_chunks(const DevGrid& g, int ox, int oy, int K, int& tiles_x, int& tiles_y) {
-    tiles_x = (g.nx + ox - 1) / ox;
-    tiles_y = (g.ny + oy - 1) / oy;
-    const int64_t cols = (int64_t)tiles_x * tiles_y;
-    int64_t best = 0;
-    int zc = g.nz;
-    for (int n = 1; n <= g.nz && n <= 4 * kCUs; ++n) {
-        const int c = (g.nz + n - 1) / n;
-        const int64_t wg = cols * ((g.nz + c - 1) / c);
-        const int64_t cost = (wg + kCUs - 1) / kCUs * (c + 2 * K + 1);
-        if (n == 1 || cost < best) {
-            best = cost;
-            zc = c;
+// count of chunks with the fewest planes walked in turn (planes).
+struct Columns {
+    int tiles_x, tiles_y, zc;
+    int64_t planes;
+};
+Columns z_chunks(const DevGrid& g, int ox, int oy, int K) {
+    Columns w{(g.nx + ox - 1) / ox, (g.ny + oy - 1) / oy, g.nz, 0};
+    const int64_t cols = (int64_t)w.tiles_x * w.tiles_y, over = 2 * K + 1;
+    // for each number of rounds the shortest chunks that fill it
+    for (int64_t r = (cols + kCUs - 1) / kCUs; w.planes == 0 || r * (1 + over) < w.planes; ++r) {
+        const int64_t n = r * kCUs / cols;  // chunks per column
+        const int c = (int)((g.nz + n - 1) / n);
+        if (w.planes == 0 || r * (c + over) < w.planes) {
+            w.planes = r * (c + over);
+            w.zc = c;
         }
+        if (c == 1) break;
     }
-    return zc;
+    return w;
 }
 
 // (a plane's byte offsets fit 31 bits)
 bool b3d_applies(const DevGrid& g) { return use_z3d(g) && (int64_t)g.nx * g.ny < ((int64_t)1 << 28); }
 
 template <typename R, int K, bool kHarm>
+Columns b3d_columns(const DevGrid& g) {
+    return z_chunks(g, 64 - 2 * K, b3_rows<R, K, kHarm>() * kWaves3 - 2 * K, K);
+}
+
+// Whether launches of K stages beat one stage a launch.  A column of a
+// workgroup is 10 to 32 rows of results whatever the grid has, so on grids of few
+// y rows (and with harmonic means, whose columns are narrowest, on some more)
+// they compute rows that are no cells: 1000 x 1 x 1000 in double takes 37 us a
+// stage in launches of 3 and 23 one by one, x 4 rows 37.7 and 38.5, x 5 rows 39
+// and 57; 64 x 1 x 20000 77 and 28.  Where a launch is mostly its start they pay
+// on any grid (256 x 1 x 256: 6.5 and 9.1).  A launch takes 1.7 us and `step` us
+// for each plane walked in turn, or the memory's rate.
+template <typename R, int K, bool kHarm>
+bool b3d_pays(const DevGrid& g, double step) {
+    const double walk = 1.7 + step * (double)b3d_columns<R, K, kHarm>(g).planes;
+    const double mem = (double)g.N * (sizeof(R) * 5 / 4.5e6);
+    return (walk > mem ? walk : mem) <= K * z3d_cost(g, kHarm ? 1 : 0, sizeof(R) == 4);
+}
+
+template <typename R, int K, bool kHarm>
 void launch_b3d_k(hipStream_t s, const DevGrid& g, B3Args<R>& a, bool keep) {
-    constexpr int rows = b3_rows<R, K, kHarm>(), waves = 8;
-    a.zc = z_chunks(g, 64 - 2 * K, rows * waves - 2 * K, K, a.tiles_x, a.tiles_y);
+    constexpr int rows = b3_rows<R, K, kHarm>(), waves = kWaves3;
+    const Columns w = b3d_columns<R, K, kHarm>(g);
+    a.tiles_x = w.tiles_x;
+    a.tiles_y = w.tiles_y;
+    a.zc = w.zc;
     const int64_t wg = (int64_t)a.tiles_x * a.tiles_y * ((g.nz + a.zc - 1) / a.zc);
     const dim3 grid((unsigned)wg), block(64 * waves);
     auto go = [&](auto mode) {
@@ -432,8 +458,20 @@ void launch_b3d_k(hipStream_t s, const DevGrid& g, B3Args<R>& a, bool keep) {
 
 }  // namespace
 
-int b3d_stages(const DevGrid& g, int count, bool f32) {
+int b3d_rows(int face, int K, bool f32) {
+    auto rows = [&](auto harm) {
+        constexpr bool h = decltype(harm)::value;
+        if (f32) return K == 4 ? b3_rows<float, 4, h>() : K == 3 ? b3_rows<float, 3, h>() : b3_rows<float, 2, h>();
+        return K == 3 ? b3_rows<double, 3, h>() : b3_rows<double, 2, h>();
+    };
+    return kWaves3 * (face == 1 ? rows(std::true_type{}) : rows(std::false_type{}));
+}
+
+int b3d_stages(const DevGrid& g, int face, int count, bool f32) {
     if (!b3d_applies(g)) return 1;
+    const bool pays = f32 ? (face == 1 ? b3d_pays<float, 4, true>(g, 2.5) : b3d_pays<float, 4, false>(g, 1.52))
+                          : (face == 1 ? b3d_pays<double, 3, true>(g, 1.9) : b3d_pays<double, 3, false>(g, 1.4));
+    if (!pays) return 1;
     const int kmax = f32 ? b3_kmax<float>() : b3_kmax<double>();
     const int launches = (count + kmax - 1) / kmax;
     return (count + launches - 1) / launches;
@@ -529,7 +567,7 @@ struct A3Args {
 
 template <int K, int ROWS, bool kAcc>
 __global__ void __launch_bounds__(512) k_adj_b3d(A3Args a) {
-    constexpr int WAVES = 8, RW = ROWS + 2, U = K + 1;
+    constexpr int WAVES = kWaves3, RW = ROWS + 2, U = K + 1;
     constexpr int OX = 64 - 2 * K, EXT_Y = WAVES * ROWS, OY = EXT_Y - 2 * K;
     // seam rows of the stages' psi and v: [buffer][stage][psi, v][wave][first / last row]
     __shared__ double sh[2][K][2][WAVES][2][64];
@@ -736,8 +774,11 @@ __global__ void __launch_bounds__(512) k_adj_b3d(A3Args a) {
 
 template <int K>
 void launch_adj_b3d_k(hipStream_t s, const DevGrid& g, A3Args& a, bool accumulate) {
-    constexpr int rows = K == 2 ? 2 : 4, waves = 8;
-    a.zc = z_chunks(g, 64 - 2 * K, rows * waves - 2 * K, K, a.tiles_x, a.tiles_y);
+    constexpr int rows = K == 2 ? 2 : 4, waves = kWaves3;
+    const Columns w = z_chunks(g, 64 - 2 * K, rows * waves - 2 * K, K);
+    a.tiles_x = w.tiles_x;
+    a.tiles_y = w.tiles_y;
+    a.zc = w.zc;
     const int64_t wg = (int64_t)a.tiles_x * a.tiles_y * ((g.nz + a.zc - 1) / a.zc);
     if (accumulate) hipLaunchKernelGGL((k_adj_b3d<K, rows, true>), dim3((unsigned)wg), dim3(64 * waves), 0, s, a);
     else hipLaunchKernelGGL((k_adj_b3d<K, rows, false>), dim3((unsigned)wg), dim3(64 * waves), 0, s, a);

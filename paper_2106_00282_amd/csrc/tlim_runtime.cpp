@@ -498,7 +498,7 @@ void run_lim_pass(tlim_ctx* c, const DevGrid& g, int face, double tau, const Pas
                 return ps.lam_dev ? tlim::StageParam{ps.lam_dev, 0.0, ps.chat[k]}
                                   : tlim::StageParam{nullptr, ps.tb[k], 0.0};
             };
-            const int k = tlim::sweeps_per_launch(g, nst - 2, true);
+            const int k = tlim::sweeps_per_launch(g, face, nst - 2, true);
             if (k > 1)
                 tlim::launch_b3d<float>(s, g, face, nullptr, c->q32, c->Lam32, c->rC32, c->wb[0], ps.at(1), k, tau,
                                         nullptr, tlim::PassSlots{}, sp(0));
@@ -509,7 +509,8 @@ void run_lim_pass(tlim_ctx* c, const DevGrid& g, int face, double tau, const Pas
             sc.launches++;
         }
         while (m < upto) {
-            int k = tlim::sweeps_per_launch(g, tlim::final32_apart(g) && m < nst - 1 ? nst - 1 - m : upto - m, true);
+            const int left = tlim::final32_apart(g) && m < nst - 1 ? nst - 1 - m : upto - m;
+            int k = tlim::sweeps_per_launch(g, face, left, true);
             bool last = !vh && m + k == nst;
             float* nxt = cur == c->wb[0] ? c->wb[1] : c->wb[0];
             int done = tlim::launch_sweeps32(s, g, face, cur, c->q32, c->Lam32, c->rC32, nxt, ps.at(m), k, last, tau,
@@ -534,7 +535,7 @@ void run_lim_pass(tlim_ctx* c, const DevGrid& g, int face, double tau, const Pas
         int pp = 0;
         const int upto = vh ? nst - 1 : nst;
         while (m < upto) {
-            int k = tlim::sweeps_per_launch(g, upto - m);
+            int k = tlim::sweeps_per_launch(g, face, upto - m);
             bool last = !vh && m + k == nst;
             double* nxt = last ? out : c->vb[pp];
             int done = tlim::launch_sweeps64(s, g, face, cur, rhs, c->Lam, c->rC, nxt, ps.at(m), k, last, tau, Tit,
@@ -1177,6 +1178,15 @@ const char* tlim_status_str(tlim_status s) {
         case TLIM_E_NUMERIC: return "TLIM_E_NUMERIC";
     }
     return "unknown";
+}
+
+// stage_plan of a grid (host only, for tests; not part of the ABI): 0, or -1
+// for invalid arguments.
+int32_t tlim_stage_plan(const tlim_grid* grid, int32_t precision, int32_t face_mean, int32_t count, int32_t coeffs,
+                        tlim::StagePlan* plan) {
+    if (tlim::check_grid(grid) || !plan || count < 1) return -1;
+    *plan = tlim::stage_plan(tlim::pack_grid(grid), face_mean, count, precision == TLIM_FP32, coeffs != 0);
+    return 0;
 }
 
 const char* tlim_last_error(const tlim_ctx* c) { return c ? c->err.c_str() : tlim::free_error.c_str(); }
@@ -2122,7 +2132,7 @@ void adj_forward_step(tlim_ctx* c, const tlim_step_opts* o, const double* lamv, 
             auto vin = [&](int m) -> const double* { return m == 0 ? T0 : st0 + (size_t)m * sf; };
             int m = 0;
             while (m < nst) {
-                int k = tlim::sweeps_per_launch(g, nst - m);
+                int k = tlim::sweeps_per_launch(g, o->face_mean, nst - m);
                 double* out = m + k == nst ? Tout : st0 + (size_t)(m + k) * sf;
                 tlim::Stages stg{nullptr, tbv.data() + m, nullptr};
                 int done = -1;
@@ -2143,7 +2153,7 @@ void adj_forward_step(tlim_ctx* c, const tlim_step_opts* o, const double* lamv, 
             const double* cur = T0;
             int pp = 0, m = 0;
             while (m < nst) {
-                int k = tlim::sweeps_per_launch(g, nst - m);
+                int k = tlim::sweeps_per_launch(g, o->face_mean, nst - m);
                 bool last = m + k == nst;
                 double* nxt = last ? Tout : c->vb[pp];
                 tlim::Stages stg{nullptr, tbv.data() + m, nullptr};

@@ -27,7 +27,16 @@ struct Stages {
 // Number of stages the next launch will advance when `count` remain (the
 // launches of a pass get equal shares, in as many launches as cost least);
 // f32: stages of the FP32 correction form.
-int sweeps_per_launch(const DevGrid& g, int count, bool f32 = false);
+int sweeps_per_launch(const DevGrid& g, int face, int count, bool f32 = false);
+
+// What the next launch of `count` remaining stages is on this grid: its kernel,
+// its stages and the extended cells of a workgroup's (3D one-stage launches: a
+// wave's) tile in x and y; coeffs: it also builds the next coefficients.
+enum { PLAN_GENERAL = 0, PLAN_LINE = 1, PLAN_TILES = 2, PLAN_MARCH = 3, PLAN_BLOCKED_MARCH = 4 };
+struct StagePlan {
+    int32_t kernel, stages, tile_x, tile_y;
+};
+StagePlan stage_plan(const DevGrid& g, int face, int count, bool f32, bool coeffs);
 
 // The grid's double launches run on the largest tiles (no CUs left idle on
 // them): where the whole-step kernel, whose tiles are always that large, can
@@ -101,8 +110,15 @@ void launch_b3d(hipStream_t s, const DevGrid& g, int face, const R* v, const R* 
                 Stages st, int K, double tau, const double* Tit, PassSlots ps,
                 StageParam sp_in = StageParam{nullptr, 0.0, 0.0}, bool keep = false, R* stages = nullptr,
                 int64_t sstride = 0);
-// Stages of the next 3D launch when `count` remain (1 where blocking does not apply).
-int b3d_stages(const DevGrid& g, int count, bool f32);
+// Stages of the next 3D launch when `count` remain (1 where blocking does not
+// apply or does not pay: the same answer for every count).
+int b3d_stages(const DevGrid& g, int face, int count, bool f32);
+// Rows of a workgroup's column in a launch of K such stages.
+int b3d_rows(int face, int K, bool f32);
+// us per stage of the one-stage launches (launch_z3d) on this grid, and the rows
+// of a wave there.
+double z3d_cost(const DevGrid& g, int face, bool f32);
+int z3d_rows(bool f32);
 // K = 1 or 2 reverse stages of the adjoint on a 3D grid in one launch
 // (arithmetic face means): psi_out = the K stages' c_m (tb psi - tau rC A' psi)
 // from psi, the face gradient and dL/dg accumulated in place into gLam and

@@ -926,7 +926,7 @@ int launch_sweeps64_keep(hipStream_t s, const DevGrid& g, int face, const double
     if (use_tb2d(g, count))
         return launch_tb2d<double>(s, g, face, v, rhs, Lam, rC, out, st, count, tau, nullptr, PassSlots{}, stages,
                                    sstride);
-    const int k = b3d_stages(g, count, false);
+    const int k = b3d_stages(g, face, count, false);
     if (k > 1) {
         launch_b3d<double>(s, g, face, v, rhs, Lam, rC, out, st, k, tau, nullptr, PassSlots{},
                            StageParam{nullptr, 0.0, 0.0}, true, stages, sstride);
@@ -937,9 +937,9 @@ int launch_sweeps64_keep(hipStream_t s, const DevGrid& g, int face, const double
 
 bool final32_apart(const DevGrid& g) { return use_z3d(g) || use_line(g); }
 
-int sweeps_per_launch(const DevGrid& g, int count, bool f32) {
+int sweeps_per_launch(const DevGrid& g, int face, int count, bool f32) {
     if (use_line(g)) return line_stages(count);
-    if (!use_tb2d(g, count)) return b3d_stages(g, count, f32);
+    if (!use_tb2d(g, count)) return b3d_stages(g, face, count, f32);
     // equal launches (a launch of K stages recomputes a ring of width K, so
     // even launches waste least), as many as cost least
     int best = 0;
@@ -954,6 +954,18 @@ int sweeps_per_launch(const DevGrid& g, int count, bool f32) {
         }
     }
     return (count + best - 1) / best;
+}
+
+StagePlan stage_plan(const DevGrid& g, int face, int count, bool f32, bool coeffs) {
+    const int k = sweeps_per_launch(g, face, count, f32);
+    if (use_tb2d(g, k)) {
+        const Shape& t = kShapeTab[best_shape(g, k, coeffs ? k + 1 : k, f32)];
+        return StagePlan{PLAN_TILES, k, t.ext_x(), t.ext_y()};
+    }
+    if (use_line(g)) return StagePlan{PLAN_LINE, k, 256, 1};
+    if (k > 1) return StagePlan{PLAN_BLOCKED_MARCH, k, 64, b3d_rows(face, k, f32)};
+    if (use_z3d(g)) return StagePlan{PLAN_MARCH, 1, 64, z3d_rows(f32)};
+    return StagePlan{PLAN_GENERAL, 1, 0, 0};
 }
 
 bool big_tiles2d(const DevGrid& g) {
@@ -977,7 +989,7 @@ int launch_sweeps64(hipStream_t s, const DevGrid& g, int face, const double* v, 
         launch_line<double>(s, g, face, v, rhs, Lam, rC, out, st, k, tau, last ? Tit : nullptr, ps);
         return k;
     }
-    if (const int k = b3d_stages(g, count, false); k > 1) {
+    if (const int k = b3d_stages(g, face, count, false); k > 1) {
         launch_b3d<double>(s, g, face, v, rhs, Lam, rC, out, st, k, tau, last ? Tit : nullptr, ps);
         return k;
     }
@@ -1016,7 +1028,7 @@ int launch_sweeps32(hipStream_t s, const DevGrid& g, int face, const float* w, c
         const int k = line_stages(count);
         launch_line<float>(s, g, face, w, qn, Lam32, rC32, out, st, k, tau, nullptr, PassSlots{});
         return k;
-    } else if (const int k = b3d_stages(g, count, true); k > 1) {
+    } else if (const int k = b3d_stages(g, face, count, true); k > 1) {
         launch_b3d<float>(s, g, face, w, qn, Lam32, rC32, out, st, k, tau, nullptr, PassSlots{});
         return k;
     } else if (use_z3d(g)) {

@@ -243,11 +243,29 @@ __global__ void __launch_bounds__(64 * kZWaves) k_z3d(Z3Args<R> a) {
 }
 
 // y rows per wave: fewer in double, to keep two waves per SIMD
-template <typename R>
-constexpr int z_rows() {
-    return sizeof(R) == 8 ? 4 : 8;
+constexpr int z_rows(bool f32) { return f32 ? 8 : 4; }
+
+// A launch's waves: columns of 64 by `rows` cells, in z chunks sized for about
+// `target` waves, 4..64 planes each.
+struct Walk {
+    int tiles_x, tiles_y, zc;
+    int64_t waves;
+};
+Walk z_walk(const DevGrid& g, int rows, int target) {
+    Walk w;
+    w.tiles_x = (g.nx + 63) / 64;
+    w.tiles_y = (g.ny + rows - 1) / rows;
+    const int64_t cols = (int64_t)w.tiles_x * w.tiles_y;
+    const int64_t zc = (int64_t)g.nz * cols / target;
+    w.zc = (int)(zc < 4 ? 4 : (zc > 64 ? 64 : zc));
+    w.waves = cols * ((g.nz + w.zc - 1) / w.zc);
+    return w;
 }
 
+// About 2048 (float) or 4096 (double) waves: fewer, longer chunks re-read
+// fewer halo planes (at 256^3 the float stage takes 83 us with 2048 waves, 88 us
+// with 4096 and 128 us with 1024, where too few waves stay in flight).
+Walk stage_walk(const DevGrid& g, bool f32) { return z_walk(g, z_rows(f32), f32 ? 2048 : 4096); }
 
 template <typename R, bool kCorr, bool kFromG = false>
 void launch_z3d_impl(hipStream_t s, const DevGrid& g, int face, const R* v, const R* G, const R* Lam, const R* rC,
@@ -276,21 +294,13 @@ void launch_z3d_impl(hipStream_t s, const DevGrid& g, int face, const R* v, cons
     a.wy = g.w[1];
     a.wz = g.w[2];
     a.face = face;
-    a.tiles_x = (g.nx + 63) / 64;
-    constexpr int rows = z_rows<R>();
-    a.tiles_y = (g.ny + rows - 1) / rows;
-    // z chunks sized for about 2048 (float) or 4096 (double) waves, 4..64
-    // planes each: fewer, longer chunks re-read fewer halo planes (at 256^3
-    // the float stage takes 83 us with 2048 waves, 88 us with 4096 and
-    // 128 us with 1024, where too few waves stay in flight)
-    const int64_t cols = (int64_t)a.tiles_x * a.tiles_y;
-    int64_t zc = (int64_t)g.nz * cols / (sizeof(R) == 4 ? 2048 : 4096);
-    zc = zc < 4 ? 4 : (zc > 64 ? 64 : zc);
-    a.zc = (int)zc;
-    const int64_t nw = cols * ((g.nz + a.zc - 1) / a.zc);
-    a.nwaves = (int)nw;
-    const unsigned blocks = (unsigned)((nw + kZWaves - 1) / kZWaves);
-    hipLaunchKernelGGL((k_z3d<R, rows, kCorr, kFromG>), dim3(blocks), dim3(64 * kZWaves), 0, s, a);
+    const Walk w = stage_walk(g, sizeof(R) == 4);
+    a.tiles_x = w.tiles_x;
+    a.tiles_y = w.tiles_y;
+    a.zc = w.zc;
+    a.nwaves = (int)w.waves;
+    const unsigned blocks = (unsigned)((w.waves + kZWaves - 1) / kZWaves);
+    hipLaunchKernelGGL((k_z3d<R, z_rows(sizeof(R) == 4), kCorr, kFromG>), dim3(blocks), dim3(64 * kZWaves), 0, s, a);
 }
 
 }  // namespace
@@ -313,6 +323,27 @@ void launch_z3d_final32(hipStream_t s, const DevGrid& g, int face, const float* 
     launch_z3d_impl<double, true>(s, g, face, nullptr, rhs, nullptr, rC, out, StageParam{nullptr, 0.0, 0.0}, tau, Tit,
                                   ps, w, Lam32);
 }
+
+// Every wave in flight takes a plane step in about `plane` us and `row` us more
+// per row of cells it holds (waves beyond the grid's last row skip theirs), two
+// waves per SIMD in turn; or the memory's rate.  Fitted to 220 grids, from one
+// y row to 300^3.
+double z3d_cost(const DevGrid& g, int face, bool f32) {
+    struct Fit {
+        double plane, row, cell;
+    };
+    constexpr Fit kFit[2][2] = {{{1.12, 0.20, 9.8e-6}, {1.84, 0.14, 8.9e-6}},
+                                {{0.84, 0.30, 2.7e-6}, {1.36, 0.34, 2.7e-6}}};  // [float][harmonic]
+    const Fit& f = kFit[f32][face == 1];
+    const Walk w = stage_walk(g, f32);
+    double rounds = (double)((w.waves + 2047) / 2048);
+    if (!f32 && face == 1) rounds = w.waves > 1536 ? (double)w.waves / 1536 : 1.0;
+    const double walk = (w.zc + 3) * rounds * (f.plane + f.row * g.ny / w.tiles_y);
+    const double mem = (double)g.N * f.cell;
+    return walk > mem ? walk : mem;
+}
+
+int z3d_rows(bool f32) { return z_rows(f32); }
 
 bool use_z3d(const DevGrid& g) { return g.nz > 1 && g.N < ((int64_t)1 << 32); }
 
