@@ -220,12 +220,14 @@ __global__ void __launch_bounds__(64 * WAVES, 2) k_tb2d_adj(AdjArgs a) {
 
 }  // namespace
 
+bool use_adj_tb2d(const DevGrid& g, int face) { return g.nz == 1 && g.ny >= EXT_Y / 2 && face == 0; }
+
 int launch_adjoint_sweeps(hipStream_t s, const DevGrid& g, int face, const double* psi_in, int first,
                           const double* Lam, const double* rC, const double* stages, const double* v0,
                           int64_t sstride, int mt,
                           double* psi_out, double* dgpsi, double* gLam, int accumulate, const double* cm,
                           const double* tb, int count, double tau, const AdjCell* cell) {
-    if (!(g.nz == 1 && g.ny >= EXT_Y / 2 && face == 0)) return -1;
+    if (!use_adj_tb2d(g, face)) return -1;
     AdjArgs a{};
     const int K = count < KMAX ? count : KMAX;
     if (cell && mt - K == 0) a.cell = *cell;

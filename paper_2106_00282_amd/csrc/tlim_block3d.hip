@@ -772,10 +772,13 @@ __global__ void __launch_bounds__(512) k_adj_b3d(A3Args a) {
     run_steps<U>(z0 - K + 1, ze, step);
 }
 
+constexpr int adj_rows(int K) { return K == 2 ? 2 : 4; }
+Columns adj_columns(const DevGrid& g, int K) { return z_chunks(g, 64 - 2 * K, adj_rows(K) * kWaves3 - 2 * K, K); }
+
 template <int K>
 void launch_adj_b3d_k(hipStream_t s, const DevGrid& g, A3Args& a, bool accumulate) {
-    constexpr int rows = K == 2 ? 2 : 4, waves = kWaves3;
-    const Columns w = z_chunks(g, 64 - 2 * K, rows * waves - 2 * K, K);
+    constexpr int rows = adj_rows(K), waves = kWaves3;
+    const Columns w = adj_columns(g, K);
     a.tiles_x = w.tiles_x;
     a.tiles_y = w.tiles_y;
     a.zc = w.zc;
@@ -792,7 +795,13 @@ __global__ void __launch_bounds__(256) k_scale_rc(int64_t n, const double* __res
 
 }  // namespace
 
-bool use_adj_b3d(const DevGrid& g, int face) { return face == 0 && b3d_applies(g); }
+// As b3d_pays: on grids of one to four y rows most of a column's 12 rows are no
+// cells (gradient of one step of two passes, two stages per launch and one:
+// 1000 x 1 x 1000 3.7 and 2.7 ms, x 3 rows 4.1 and 4.5; 64 x 1 x 20000 7.8 and
+// 4.6 ms; 256 x 1 x 256 0.67 and 0.74).
+bool use_adj_b3d(const DevGrid& g, int face) {
+    return face == 0 && b3d_applies(g) && 1.7 + 1.6 * (double)adj_columns(g, 2).planes <= 2.0 * adj_z3d_cost(g);
+}
 
 void launch_psi_from_lambda(hipStream_t s, int64_t n, const double* lam, const double* rC, double* psi) {
     const int64_t b = (n + 255) / 256;

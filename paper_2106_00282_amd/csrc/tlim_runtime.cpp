@@ -1189,6 +1189,11 @@ int32_t tlim_stage_plan(const tlim_grid* grid, int32_t precision, int32_t face_m
     return 0;
 }
 
+// reverse_plan of a grid (as tlim_stage_plan), -1 for invalid arguments.
+int32_t tlim_reverse_plan(const tlim_grid* grid, int32_t face_mean) {
+    return tlim::check_grid(grid) ? -1 : tlim::reverse_plan(tlim::pack_grid(grid), face_mean);
+}
+
 const char* tlim_last_error(const tlim_ctx* c) { return c ? c->err.c_str() : tlim::free_error.c_str(); }
 
 tlim_status tlim_create(const tlim_grid* grid, int32_t precision, void* hip_stream, tlim_ctx** out) {
@@ -2361,6 +2366,23 @@ tlim_status tlim_adjoint_parabolic(tlim_ctx* c, const tlim_step_opts* o, int32_t
                     cur = bufs[pp];
                     pp ^= 1;
                     m -= k;
+                }
+                psi_form = true;
+            }
+            if (!psi_form && tlim::use_adj_z3d(g, o->face_mean)) {
+                // one stage per launch where blocking does not pay
+                tlim::launch_fill(s, dg, 0.0, N);
+                tlim::launch_fill(s, gLam, 0.0, N);
+                tlim::launch_psi_from_lambda(s, N, cur, c->rC, bufs[pp]);
+                cur = bufs[pp];
+                pp ^= 1;
+                for (int m = nst; m >= 1; --m) {
+                    const double tb = o->dt * b[m - 1];
+                    const double* vprev = m == 1 ? T0 : st0 + (size_t)(m - 1) * sf;
+                    tlim::launch_adj_z3d(s, g, cur, vprev, Lam, c->rC, bufs[pp], dg, gLam, 1.0 / (1.0 + tb), tb,
+                                         o->dt);
+                    cur = bufs[pp];
+                    pp ^= 1;
                 }
                 psi_form = true;
             }

@@ -37,6 +37,7 @@ struct StagePlan {
     int32_t kernel, stages, tile_x, tile_y;
 };
 StagePlan stage_plan(const DevGrid& g, int face, int count, bool f32, bool coeffs);
+int reverse_plan(const DevGrid& g, int face);  // the adjoint's reverse stages: PLAN_*
 
 // The grid's double launches run on the largest tiles (no CUs left idle on
 // them): where the whole-step kernel, whose tiles are always that large, can
@@ -130,6 +131,13 @@ void launch_psi_from_lambda(hipStream_t s, int64_t n, const double* lam, const d
 void launch_adj_b3d(hipStream_t s, const DevGrid& g, int K, const double* psi, const double* const v[2],
                     const double* Lam, const double* rC, double* psi_out, double* dgpsi, double* gLam,
                     const double cm[2], const double tb[2], double tau, int accumulate);
+// One such stage by z-marching waves (tlim_sweep3d.hip), where the blocked form
+// does not pay; dgpsi and gLam are accumulated in place (zero before the first).
+bool use_adj_z3d(const DevGrid& g, int face);
+double adj_z3d_cost(const DevGrid& g);  // us per stage
+void launch_adj_z3d(hipStream_t s, const DevGrid& g, const double* psi, const double* vprev, const double* Lam,
+                    const double* rC, double* psi_out, double* dgpsi, double* gLam, double cm, double tb,
+                    double tau);
 // The first two float stages of an FP32 pass that starts from w = 0 on a 3D
 // grid in one launch: stage 0 gives c_0 qn exactly, so the launch runs stage
 // 1 on that input read from qn (sp0, sp1: the two stages' parameters).
@@ -175,6 +183,7 @@ struct AdjCell {
     double* k0a;           // accumulator rows of the dL/dk0 sums
     double* k0b;
 };
+bool use_adj_tb2d(const DevGrid& g, int face);
 int launch_adjoint_sweeps(hipStream_t s, const DevGrid& g, int face, const double* psi_in, int first,
                           const double* Lam, const double* rC, const double* stages, const double* v0,
                           int64_t sstride, int mt,

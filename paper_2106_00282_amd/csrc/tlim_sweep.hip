@@ -968,6 +968,12 @@ StagePlan stage_plan(const DevGrid& g, int face, int count, bool f32, bool coeff
     return StagePlan{PLAN_GENERAL, 1, 0, 0};
 }
 
+int reverse_plan(const DevGrid& g, int face) {
+    if (use_adj_tb2d(g, face)) return PLAN_TILES;
+    if (use_adj_b3d(g, face)) return PLAN_BLOCKED_MARCH;
+    return use_adj_z3d(g, face) ? PLAN_MARCH : PLAN_GENERAL;
+}
+
 bool big_tiles2d(const DevGrid& g) {
     if (!use_tb2d(g, 8)) return false;
     const int shape = best_shape(g, 8, 9, false);

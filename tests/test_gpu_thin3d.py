@@ -5,7 +5,7 @@ import pytest
 
 from paper_2106_00282_amd import workloads as W
 from _cases import oracle_dt, rel_err, run_gpu, run_oracle
-from test_stage_plan import MARCH, stage_plan
+from test_stage_plan import MARCH, reverse_plan, stage_plan
 
 pytestmark = pytest.mark.gpu
 
@@ -28,4 +28,36 @@ def test_thin_grids(shape, walls, face, precision):
     tol = 1e-12 if precision == "fp64" else 1e-5
     for k in ("T1", "alpha2", "u", "v", "w"):
         assert rel_err(fg[k], fo[k]) <= tol, k
+    s.close()
+
+
+@pytest.mark.parametrize("shape,walls", [((700, 1, 700), (1, 0, 0)), ((65, 2, 4099), (0, 1, 1)), ((5, 1, 20000), (0, 0, 0))])
+def test_thin_grids_adjoint(shape, walls):
+    """The gradient of two steps against the oracle's adjoint, with the steps of
+    the interval recomputed each or kept (the same bits)."""
+    import numpy as np
+    import torch
+    from oracle import oracle as orc
+    from paper_2106_00282_amd.tlim import StepOpts
+    from _cases import make_solver
+    wl = W.interface3d(max(shape[0], shape[2]) // 8, shape=shape)
+    wl["h"] = (1.0 / shape[0],) * 3
+    wl["bc"] = tuple(W.ADIABATIC if w else W.PERIODIC for w in walls)
+    assert reverse_plan(shape) == MARCH
+    tau, _ = oracle_dt(orc, wl)
+    s = make_solver(wl)
+    opts = StepOpts(dt=tau, passes=2)
+    ckpt, lam = s.forward_checkpointed(opts, 2, 2)
+    seed = np.random.default_rng(3).standard_normal(ckpt.shape[1:])
+    dT0, dk0 = s.adjoint(opts, 2, 2, ckpt, lam, torch.from_numpy(seed), keep_interval=False)
+    s._adj_ws = None
+    kept, dk1 = s.adjoint(opts, 2, 2, ckpt, lam, torch.from_numpy(seed), keep_interval=True)
+    assert torch.equal(kept, dT0)
+    g = orc.make_grid(wl["n"], wl["h"], wl["bc"])
+    f = wl["fields"]
+    oT, ok = orc.heat_adjoint(g, wl["phases"], orc.StepOpts(tau=tau, passes=2), 2, np.array(lam), f["alpha2"], f["m1"],
+                              f["m2"], f["T1"], seed)[:2]
+    assert rel_err(dT0.cpu().numpy(), oT) <= 1e-12
+    for dk in (dk0, dk1):  # (sums by atomics: not bit for bit)
+        assert max(abs(dk[k] - ok[k]) for k in range(2)) <= 1e-10 * max(abs(x) for x in ok)
     s.close()

@@ -44,3 +44,16 @@ def test_flat_grids():
     assert stage_plan((1000,)).kernel == LINE
     assert stage_plan((100, 31)).kernel == GENERAL
     assert stage_plan((100, 32)).kernel == TILES
+
+
+def reverse_plan(n, face=0):
+    return tlim.load_library().tlim_reverse_plan(ctypes.byref(tlim.make_grid(n)), face)
+
+
+@pytest.mark.parametrize("n,kernel", [((1000, 1, 1000), MARCH), ((64, 3, 20000), MARCH), ((700, 2, 700), MARCH),
+                                      ((20000, 20000, 2), MARCH), ((1000, 4, 1000), BLOCKED_MARCH),
+                                      ((128, 128, 128), BLOCKED_MARCH), ((256, 1, 256), BLOCKED_MARCH),
+                                      ((100, 40), TILES), ((100, 31), GENERAL), ((1000,), GENERAL)])
+def test_reverse_stages(n, kernel):
+    assert reverse_plan(n) == kernel
+    assert reverse_plan(n, face=1) == GENERAL
