@@ -67,7 +67,7 @@ struct Coef2DArgs {
     double wx, wy, tau, eps;
     int face, rebuild, tiles_x, strips;
     // 3D grids
-    int nz, perz, tiles_y, zc;
+    int nz, perz, tiles_y, zc, waves;
     double wz;
 };
 
@@ -190,8 +190,8 @@ __global__ void __launch_bounds__(64 * kWaves) k_coeffs2d(Coef2DArgs a) {
     }
 }
 
-// 3D grids: the same per-cell work.  A workgroup of four waves owns 62 columns
-// by 4 kRows3 rows and marches through a chunk of z planes, each wave keeping the
+// 3D grids: the same per-cell work.  A workgroup of four waves (fewer on grids of
+// up to six rows) owns 62 columns by 4 kRows3 rows and marches through a chunk of z planes, each wave keeping the
 // conductivities (and g) of its kRows3 rows in the previous, current and next
 // plane in registers.  Rows next to another wave's come through LDS (one
 // barrier a plane, two buffers); the rows beyond the workgroup's are built by
@@ -202,7 +202,10 @@ __global__ void __launch_bounds__(64 * kWaves) k_coeffs2d(Coef2DArgs a) {
 // on 4 rows to write 2, and that arithmetic was the bound: 1743 us against 1322
 // at 512^3, 327 against 220 at 256^3, 37 against 29 at 128^3; with the
 // relaxation 3242 against 2636, 448 against 364 and 57 against 46.  Four rows a
-// wave need half again the registers and are slower (1450 us at 512^3).
+// wave need half again the registers and are slower (1450 us at 512^3).  Waves
+// past the last row would evaluate the laws all the same: at 1000 x 1 x 1000 four
+// took 56 us (92 with the relaxation) and one takes 24 (40); at 1000 x 4 x 1000 73
+// (116), and two take 46 (86).
 constexpr int kRows3 = 2;
 
 template <bool kRelax, bool kSH>
@@ -210,6 +213,7 @@ __global__ void __launch_bounds__(64 * kWaves) k_coeffs3d(Coef2DArgs a) {
     constexpr int kRO = kRows3;
     __shared__ double sL[2][kWaves][2][64], sg[2][kWaves][2][64];  // [plane parity][wave][first, last row]
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int nw = a.waves;
     const int wid = blockIdx.x;  // launch order: XCD order measured up to 20% slower
     const int tx = wid % a.tiles_x, rest = wid / a.tiles_x;
     const int ty = rest % a.tiles_y, tz = rest / a.tiles_y;
@@ -219,10 +223,12 @@ __global__ void __launch_bounds__(64 * kWaves) k_coeffs3d(Coef2DArgs a) {
     const bool out_lane = lane >= 1 && lane <= kOut && xg < nx;
     const bool fL = a.perx ? nx > 1 : xg > 0;
     const bool fR = a.perx ? nx > 1 : xg < nx - 1;
-    const int y0 = (ty * kWaves + w) * kRO, z0 = tz * a.zc;
+    const int y0 = (ty * nw + w) * kRO, z0 = tz * a.zc;
     const int z1 = z0 + a.zc < nz ? z0 + a.zc : nz;
     const bool q = a.q32 != nullptr;
-    const bool halo = w == 0 || w == kWaves - 1;  // this wave builds the row before or after its own as well
+    // this wave builds the row before or after its own as well (a single wave has
+    // no other rows: two periodic rows are each other's neighbours)
+    const bool halo = nw > 1 && (w == 0 || w == nw - 1);
 
     // 32-bit element offsets (the launcher requires N < 2^32); row kRO: the halo row
     unsigned rowoff[kRO + 1];
@@ -283,12 +289,13 @@ __global__ void __launch_bounds__(64 * kWaves) k_coeffs3d(Coef2DArgs a) {
         const bool fB = a.perz ? nz > 1 : z > 0;
         const bool fF = a.perz ? nz > 1 : z < nz - 1;
         // the rows before and after this wave's own
-        const double Ldn = w == 0 ? Lc[kRO] : sL[b][w - (w > 0)][1][lane];
-        const double Lup = w == kWaves - 1 ? Lc[kRO] : sL[b][w + (w < kWaves - 1)][0][lane];
+        const int wdn = w > 0 ? w - 1 : nw - 1, wup = w < nw - 1 ? w + 1 : 0;
+        const double Ldn = w == 0 && nw > 1 ? Lc[kRO] : sL[b][wdn][1][lane];
+        const double Lup = w == nw - 1 && nw > 1 ? Lc[kRO] : sL[b][wup][0][lane];
         double gdn = 0.0, gup = 0.0;
         if (q) {
-            gdn = w == 0 ? gc[kRO] : sg[b][w - (w > 0)][1][lane];
-            gup = w == kWaves - 1 ? gc[kRO] : sg[b][w + (w < kWaves - 1)][0][lane];
+            gdn = w == 0 && nw > 1 ? gc[kRO] : sg[b][wdn][1][lane];
+            gup = w == nw - 1 && nw > 1 ? gc[kRO] : sg[b][wup][0][lane];
         }
 #pragma unroll
         for (int r = 0; r < kRO; ++r) {
@@ -355,7 +362,7 @@ __global__ void __launch_bounds__(64 * kWaves) k_coeffs3d(Coef2DArgs a) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) bound = fmax(bound, __shfl_xor(bound, o, 64));
     if (lane == 0) {
-        const int sl = (wid * kWaves + w) % kSlots;
+        const int sl = (int)(((int64_t)wid * nw + w) % kSlots);
         atomicMax((unsigned long long*)(a.lam + sl), (unsigned long long)__double_as_longlong(bound + 0.0));
     }
 }
@@ -643,23 +650,25 @@ void launch_coeffs2d(hipStream_t s, const DevGrid& g, const DevPhases& ph, doubl
     a.nz = g.nz;
     a.perz = g.per[2];
     a.wz = g.w[2];
-    a.tiles_y = (g.ny + kWaves * kRows3 - 1) / (kWaves * kRows3);
+    a.waves = (g.ny + kRows3 - 1) / kRows3;
+    if (a.waves > kWaves) a.waves = kWaves;
+    a.tiles_y = (g.ny + a.waves * kRows3 - 1) / (a.waves * kRows3);
     // z chunks sized for about 4096 waves, at least 4 planes each and at most
     // 16: the workgroups in flight then work on neighbouring planes.  With the
     // relaxation's ten streams 8 are better (512^3: 2636 us against 2755 with 16
     // and 3560 with 64; without it 1382, 1322 and 1350).
     const int64_t cols = (int64_t)a.tiles_x * a.tiles_y;
     const int64_t cap = T2_relax ? 8 : 16;
-    int64_t zc = (int64_t)g.nz * cols * kWaves / 4096;
+    int64_t zc = (int64_t)g.nz * cols * a.waves / 4096;
     zc = zc < 4 ? 4 : (zc > cap ? cap : zc);
     a.zc = (int)zc;
     const unsigned blocks = (unsigned)(cols * ((g.nz + a.zc - 1) / a.zc));
     if (ph.spitzer) {
-        if (T2_relax) hipLaunchKernelGGL((k_coeffs3d<true, true>), dim3(blocks), dim3(64 * kWaves), 0, s, a);
-        else hipLaunchKernelGGL((k_coeffs3d<false, true>), dim3(blocks), dim3(64 * kWaves), 0, s, a);
+        if (T2_relax) hipLaunchKernelGGL((k_coeffs3d<true, true>), dim3(blocks), dim3(64 * a.waves), 0, s, a);
+        else hipLaunchKernelGGL((k_coeffs3d<false, true>), dim3(blocks), dim3(64 * a.waves), 0, s, a);
     } else {
-        if (T2_relax) hipLaunchKernelGGL((k_coeffs3d<true, false>), dim3(blocks), dim3(64 * kWaves), 0, s, a);
-        else hipLaunchKernelGGL((k_coeffs3d<false, false>), dim3(blocks), dim3(64 * kWaves), 0, s, a);
+        if (T2_relax) hipLaunchKernelGGL((k_coeffs3d<true, false>), dim3(blocks), dim3(64 * a.waves), 0, s, a);
+        else hipLaunchKernelGGL((k_coeffs3d<false, false>), dim3(blocks), dim3(64 * a.waves), 0, s, a);
     }
 }
 

@@ -61,3 +61,33 @@ def test_thin_grids_adjoint(shape, walls):
     for dk in (dk0, dk1):  # (sums by atomics: not bit for bit)
         assert max(abs(dk[k] - ok[k]) for k in range(2)) <= 1e-10 * max(abs(x) for x in ok)
     s.close()
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("ny,wall,face,spitzer", [(1, 0, 0, False), (1, 1, 1, True), (2, 0, 1, False), (2, 1, 0, False),
+                                                  (3, 0, 0, True), (4, 0, 0, False), (4, 1, 1, False), (5, 0, 1, False),
+                                                  (6, 0, 0, False), (7, 1, 0, False)])
+def test_coefficients_of_few_rows(ny, wall, face, spitzer, precision):
+    """Workgroups of one to three waves build the coefficients (lambda_G of the
+    first pass to 1e-13)."""
+    import numpy as np
+    from oracle import oracle as orc
+    shape = (63, ny, 19)
+    wl = W.bubbles3d(63, shape=shape)
+    if spitzer:
+        wl["phases"] = W.spitzer_phases(wl["phases"])
+    for c in "uvw":
+        wl["fields"].pop(c, None)
+    wl["bc"] = (W.PERIODIC, W.ADIABATIC if wall else W.PERIODIC, W.PERIODIC)
+    wl["fields"]["T2"] = np.ascontiguousarray(1.2 * wl["fields"]["T1"])
+    wl["dt_factor"] = 20.0
+    tau, _ = oracle_dt(orc, wl)
+    fo, ro = run_oracle(orc, wl, tau, 2, passes=2, viscous=False, face_mean=face)
+    print(f"case {shape} wall={wall} face={face} spitzer={spitzer} {precision}", flush=True)
+    fg, rg, s = run_gpu(wl, tau, 2, passes=2, viscous=False, precision=precision, face_mean=face)
+    assert abs(rg[0]["lambda_G"][0] - ro[0]["lambda_G"][0]) <= 1e-13 * ro[0]["lambda_G"][0]
+    assert [r["P"] for r in rg] == [r["P"] for r in ro]
+    tol = 1e-12 if precision == "fp64" else 1e-5
+    for k in ("T1", "alpha2"):
+        assert rel_err(fg[k], fo[k]) <= tol, k
+    s.close()
