@@ -1,12 +1,13 @@
 """GPU parity of the 3D kernels that advance several LIM stages per launch.
 
 A workgroup writes the inner 64 - 2K by rows - 2K cells of its column (K = 2 or
-3 stages) and walks a chunk of planes with K planes more on either side, so
-the shapes below sit at the edges of those tiles (58 and 60 x cells; 18, 28,
-58 and 60 rows), leave one-cell remainders, are thinner than the halo, or are
-a single plane chunk.  dt factors give passes whose stage counts leave every
-remainder (launches of 3, 2 and 1 stages).  Bars as everywhere: FP64 1e-12,
-FP32 form 1e-5 per field against the FP64 oracle (max-norm, relative)."""
+3 stages in double, up to 4 in float; 10 to 56 rows) and walks a chunk of planes
+with K planes more on either side; the shapes below have sides near such tiles
+(58 and 60 x cells, 18 and 28 rows), leave small remainders, are thinner than
+the halo, or are a single plane chunk (every kernel's own tile edges are in
+test_gpu_block3d_edges.py).  dt factors give passes whose stage counts leave every
+remainder.  Bars as everywhere: FP64 1e-12, FP32 form 1e-5 per field against the
+FP64 oracle (max-norm, relative)."""
 import numpy as np
 import pytest
 
