@@ -368,33 +368,29 @@ __global__ void __launch_bounds__(64 * NW, 4) k_tb2d(TBArgs<R> a) {
         ptb = a.lam ? a.taud * lamv * a.chat[lane] : a.tb[lane];
         pcm = 1.0 / (1.0 + ptb);
     }
-    // In double the stages run on V^(s) = Q_s v^(s), Q_s = prod_{k<s} (1 + tau b_k):
+    // In double the stages before the launch's last run on V^(s) = Q_s v^(s),
+    // Q_s = prod_{k<s} (1 + tau b_k):
     //   V^(s+1) = Q_s G + tau b_s V^(s) - sum_f kappa_f (V_a - V_f)^(s),
     // one product per cell and stage less than with the factor c_s.  Lane s
-    // holds Q_s and 1/Q_(s+1).  The products are carried as pairs (hi + lo): each
-    // Q_s is then rounded once, and what Q_(s+1) / Q_s is off from 1 + tau b_s, alike in
-    // every cell and launch, does not add up over a run (products in one double
-    // left 2.5e-14 after 10 steps where the factors c_s left 4e-15).
-    double pQ = 1.0, piQ = 1.0, Qk = 1.0;
+    // holds Q_s and 1/Q_(s+1).  The last stage takes the scale off the
+    // differences, not off the result,
+    //   v^(K) = c (G + (tau b V - sum_f kappa_f (V_a - V_f)) / Q),
+    // so that the final one (b = 0) is G minus differences as in every other
+    // kernel.  G Q / Q left all cells off by one factor (up to 1e-16 per step,
+    // which nothing wears off: 6e-16 of T after 5 steps at 768^2, and a gradient
+    // through them 6.0e-15 from 64-bit arithmetic instead of 3.1e-15), and
+    // a uniform T was no equilibrium.
+    double pQ = 1.0, piQ = 1.0;
     if constexpr (!kFloat) {
         double hi = 1.0 + ptb;  // inclusive product over the lanes up to this one
-        const double bb = hi - 1.0;
-        double lo = (1.0 - (hi - bb)) + (ptb - bb);
 #pragma unroll
         for (int o = 1; o < 16; o <<= 1) {
-            const double uh = __shfl_up(hi, o, 64), ul = __shfl_up(lo, o, 64);
-            const double p = hi * uh;
-            const double e = fma(hi, uh, -p) + fma(hi, ul, lo * uh);
-            const double q = p + e;
-            if (lane >= o) {
-                lo = e - (q - p);
-                hi = q;
-            }
+            const double up = __shfl_up(hi, o, 64);
+            if (lane >= o) hi *= up;
         }
         const double below = __shfl_up(hi, 1, 64);
         pQ = lane == 0 ? 1.0 : below;
         piQ = 1.0 / hi;
-        Qk = lane_value(hi, K - 1);
     }
     // Stage s exchanges the seam rows through LDS buffer (s+1)&1; buffer 0
     // held the Lambda seams, whose reads all precede the first barrier below.
@@ -412,7 +408,8 @@ __global__ void __launch_bounds__(64 * NW, 4) k_tb2d(TBArgs<R> a) {
             for (int j = 0; j < C; ++j) v[r][j] = cm0 * G[r][j];
         s0 = 1;
     }
-    for (int s = s0; s < Kin; ++s) {
+    auto stage = [&](int s, auto scale) {  // scale: the last stage of a double launch
+        constexpr bool kScale = decltype(scale)::value;
         // the first stage run writes buffer 1 (buffer 0 held the Lambda seams)
         const int buf = (s - s0 + 1) & 1;
 #pragma unroll
@@ -428,7 +425,8 @@ __global__ void __launch_bounds__(64 * NW, 4) k_tb2d(TBArgs<R> a) {
             vup[j] = sh_lo[buf][wup][j][lane];
         }
         const double tbd = lane_value(ptb, s);
-        const R cm = (R)lane_value(kFloat ? pcm : pQ, s), tb = (R)tbd;
+        const R cm = (R)lane_value(kFloat || kScale ? pcm : pQ, s), tb = (R)tbd;
+        const R iQ = kScale && s > 0 ? (R)lane_value(piQ, s > 0 ? s - 1 : 0) : R(1);
         // Each face difference is formed once and shared by the face's two
         // cells: c - c_left is minus the left neighbour's c - c_right, and
         // c - c_below minus the row below's c - c_above (exact in floating
@@ -458,13 +456,15 @@ __global__ void __launch_bounds__(64 * NW, 4) k_tb2d(TBArgs<R> a) {
                 if constexpr (kGinLds) Gr = sG[wv * RW + r][j][lane];
                 else Gr = G[r][j];
                 if constexpr (kFloat) v[r][j] = cm * (Gr + tb * c - S);
+                else if constexpr (kScale) v[r][j] = cm * fma(tb * c - S, iQ, Gr);
                 else v[r][j] = cm * Gr + (tb * c - S);
                 ddn[j] = -dup;
             }
         }
         // the output cells are exact after every stage: keep the intermediate
-        // stages when asked (the adjoint's recomputation)
-        if (kKeep && s + 1 < K) {
+        // stages when asked (the adjoint's recomputation; without the test of
+        // the pointer, and with the rows' stores interleaved, this spills)
+        if (kKeep && !kScale && a.stages != nullptr) {
             const R iq = (R)lane_value(piQ, s);
             R* dst = a.stages + (int64_t)(s + 1) * a.sstride;
 #pragma unroll
@@ -473,17 +473,12 @@ __global__ void __launch_bounds__(64 * NW, 4) k_tb2d(TBArgs<R> a) {
 #pragma unroll
                 for (int j = 0; j < C; ++j) x[j] = v[r][j] * iq;
                 if (yout(r)) put(dst, r, x);
+                __builtin_amdgcn_sched_barrier(0);
             }
         }
-    }
-    if constexpr (!kFloat) {
-        // (1/Q_K and what its rounding left out)
-        const double iq = lane_value(piQ, K - 1), ir = iq * fma(-Qk, iq, 1.0);
-#pragma unroll
-        for (int r = 0; r < RW; ++r)
-#pragma unroll
-            for (int j = 0; j < C; ++j) v[r][j] = fma(v[r][j], iq, v[r][j] * ir);
-    }
+    };
+    for (int s = s0; s < (kFloat ? Kin : K - 1); ++s) stage(s, std::false_type{});
+    if constexpr (!kFloat) stage(K - 1, std::true_type{});
     // Final stage (b = 0) of the FP32 correction form, in double on v = g + w:
     // T = g - tau rC64 sum_f w_f mean(Lambda'_a, Lambda'_b) (v_a - v_b), with
     // Lambda' the float conductivities, into Tfin (every cell of the tile:
