@@ -1,6 +1,6 @@
 // Launchers of the LIM stages (eq. LIM).  One call advances up to `count`
 // consecutive stages and returns how many it did (>= 1, equal to
-// sweeps_per_launch(g, count)); the result is in `out`.  Several stages per
+// sweeps_per_launch(g, face, count)); the result is in `out`.  Several stages per
 // launch are fused where the grid allows (temporal blocking), otherwise one
 // stage is launched.  In FP64 the final stage (b = 0, flux form) may be among
 // them: a launch with last = true ends the pass and, when Tit != NULL, also

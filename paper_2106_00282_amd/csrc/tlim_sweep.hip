@@ -150,8 +150,8 @@ struct TBArgs {
 
 // kSH: the conductivities built in the epilogue follow the Spitzer-Harm law
 // in some phase (its logarithms would otherwise take registers from the
-// power-law kernels).  C: cells per lane along x (1: 64-wide tiles of 8 rows
-// per wave; 2: 128-wide tiles of 4 rows per wave, lane l owning cells 2l and
+// power-law kernels).  C: cells per lane along x (1: 64-wide tiles of 8, 4 or 2
+// rows per wave; 2: 128-wide tiles of 4 rows per wave, lane l owning cells 2l and
 // 2l + 1, so that one of each cell's x-neighbours is in the lane itself).
 template <typename R, int NW, int RW, int C, bool kKeep, bool kSH, bool kHarm>
 __global__ void __launch_bounds__(64 * NW, 4) k_tb2d(TBArgs<R> a) {
@@ -258,7 +258,7 @@ __global__ void __launch_bounds__(64 * NW, 4) k_tb2d(TBArgs<R> a) {
     // gives c_0 G exactly: v is then not read, and that stage is c_0 G.
     const bool vz = kFloat && !kKeep && a.vzero && a.v != a.G && (fin ? K - 1 : K) >= 1;
     // In double the source G lives in LDS (read once per cell and stage):
-    // with 8 rows per wave the four kappa and v already take 80 of the 128
+    // with 8 cells per lane the four kappa and v already take 80 of the 128
     // VGPRs that four waves per SIMD leave, and G in registers spills.
     constexpr bool kGinLds = !kFloat && RW * C == 8;
     __shared__ R sG[kGinLds ? EXT_Y : 1][C][64];
